@@ -85,14 +85,12 @@ void orloj_destroy(orloj_ctx *ctx);
  * first. */
 int orloj_set_stream(orloj_ctx *ctx, void *hip_stream);
 
-/* Prefix steps one score workgroup takes (orloj_score_candidates and
- * orloj_score_candidates_affine).  A (model, batch size) pair's prefix
- * lengths are scored in sequence; when a launch has too few pairs to fill
- * the GPU, splitting them into chunks of `steps` (each chunk first rebuilds
- * the batch CDF of the prefixes before it) shortens the launch.  -1 (the
- * default): chosen per launch from the queue lengths and the device's
- * compute units; 0: never split; k > 0: chunks of k.  The results are the
- * same bits whatever the setting.  ORLOJ_E_INVALID for steps < -1. */
+/* Prefix steps one score workgroup takes: -1 (the default) automatic, 0 never
+ * split, k > 0 chunks of k.  The setting is accepted and has no effect: a
+ * launch with too few (model, batch size) pairs to fill the GPU is split over
+ * blocks of 64 prefix lengths and over the bins, whatever it is, and the
+ * results are the same bits for every value.  ORLOJ_E_INVALID for
+ * steps < -1. */
 int orloj_set_score_chunk(orloj_ctx *ctx, int32_t steps);
 
 /* Text of the last error of `ctx` (never NULL; "" when none). */
@@ -225,7 +223,8 @@ int orloj_score_candidates(orloj_ctx *ctx, const orloj_grid *grid, const float *
  * error (orloj_sync); that model's requests then score as dead.
  * The sums of 1 - G behind E[X] do not depend on the batch size, so they
  * are formed once per (model, prefix length) into a scratch block the
- * context owns (M x ceil(K / 256) x the longest prefix floats).  The
+ * context owns (M x ceil(K / 256) x the longest prefix floats, doubles where
+ * that is at most 2^19 sums and the launch is small).  The
  * first call that needs a larger block waits for the context's
  * stream, frees the old block and allocates the new one (ORLOJ_E_NOMEM if
  * that fails); the block is reused by later calls and freed by
@@ -385,10 +384,8 @@ int orloj_accumulate(orloj_ctx *ctx, const orloj_grid *grid, int64_t n_samples,
  * largest batch size: no longer prefix is a candidate), uploads every idle
  * model's queue in one copy from pinned memory, scores and selects (the
  * outputs of orloj_score_candidates and orloj_select_batch, TRIANGLE
- * prefixes, bit for bit; in a round small enough to take its E sums from a
- * pre-pass, that pre-pass shares the score launch and the selection kernel
- * finishes E[L_B] and the scores), reads the selections back and removes
- * the selected members from their queues.
+ * prefixes, bit for bit), reads the selections back and removes the selected
+ * members from their queues.
  *
  * orloj_sched_create copies the grid (its d_bin_width_ms must stay valid)
  * and keeps d_ccdf / d_support (orloj_build_cdfs' table of the model's

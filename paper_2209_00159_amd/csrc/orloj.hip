@@ -9,6 +9,9 @@
 //                  position of the members' CDF rows into the batch CDF,
 //                  E[L_B], finish probabilities and Eq. (2) priorities of
 //                  every prefix candidate, all in one pass
+//   turned_kernel  the same outputs in launches too small to fill the chip:
+//                  a workgroup's waves split the bins, lanes hold prefix
+//                  lengths
 //   emax_kernel    affine mode: the sums behind E[L_B], once per prefix
 //                  length instead of once per batch size
 //   select_kernel  one workgroup per model: argmax over its candidates
@@ -31,9 +34,11 @@
 #include <string.h>
 
 #include <algorithm>
+#include <atomic>
 #include <mutex>
 #include <new>
 #include <type_traits>
+#include <utility>
 
 #include "../../include/orloj.h"
 #include "orloj_ctx.h"
@@ -317,9 +322,6 @@ struct ScoreArgs {
     float* psum;               // affine mode: [M][np_e][maxcap] panel sums of 1 - G
     int np_e;                  // panels of those sums (emax_kernel's panel width)
     int* err;
-    int defer;                 // 1: write the priority sum to S, leave E[L_B] and S to the selection
-    int chunk;                 // prefix lengths scored per workgroup (0: all of them)
-    int nchunk;                // workgroups per (model, batch size)
     double b;
     int M, C, K, nbs, rect, maxcap;
     int Mg;                    // models the grid covers: M, or the listed ones
@@ -569,13 +571,10 @@ struct LaneCarry64 {
 // same wave then reads to score those members.  Rows are prefetched PF
 // iterations ahead through a register ring.  Panels past the last member's
 // deadline need only the sums of 1 - G: a second, lean loop takes them
-// (tabulated mode).  A workgroup may take a chunk of the steps only, after
-// warm-up steps that rebuild G over the steps before it.
+// (tabulated mode).  Launches with too few workgroups to fill the chip go to
+// turned_kernel.
 #ifndef ORLOJ_SCORE_PREFETCH
 #define ORLOJ_SCORE_PREFETCH 2   // iterations a row is loaded ahead of its use
-#endif
-#ifndef ORLOJ_SPLIT_PREFETCH
-#define ORLOJ_SPLIT_PREFETCH 4   // the same in launches with an E pre-pass
 #endif
 #ifndef ORLOJ_EONLY_PREFETCH
 #define ORLOJ_EONLY_PREFETCH 3   // iterations ahead in the E-only panels' loop
@@ -586,12 +585,8 @@ struct LaneCarry64 {
 #ifndef ORLOJ_EONLY_LDS_CACHE
 #define ORLOJ_EONLY_LDS_CACHE 3  // further classes whose slices it keeps in LDS
 #endif
-#ifndef ORLOJ_WARMUP_PREFETCH
-#define ORLOJ_WARMUP_PREFETCH 4  // steps ahead in a chunk's warm-up loop
-#endif
-template <int CPL, int PF, bool EXACT, int CR, bool AFF, bool ESPLIT>
+template <int CPL, int PF, bool EXACT, int CR, bool AFF>
 __device__ __forceinline__ void score_wave(const ScoreArgs& a, const unsigned bid) {
-    static_assert(ESPLIT || !AFF, "the affine mode takes its E sums from emax_kernel");
     using Q = Quarters<CPL>;
     constexpr int PW = 64 * CPL;                   // bins per panel
     extern __shared__ __align__(16) unsigned char smem_raw[];
@@ -605,33 +600,21 @@ __device__ __forceinline__ void score_wave(const ScoreArgs& a, const unsigned bi
 
     const int lane = threadIdx.x;
 
-    // Largest batch sizes first, and their last chunks first: those
-    // workgroups run longest.
-    const unsigned per_bs = (unsigned)a.Mg * (unsigned)a.nchunk;
-    const int bi = a.nbs - 1 - (int)(bid / per_bs);
-    const unsigned rem = bid % per_bs;
-    const int kc = a.nchunk - 1 - (int)(rem / (unsigned)a.Mg);
-    const int q = grid_model(a, rem % (unsigned)a.Mg);
+    // Largest batch sizes first: those workgroups run longest.
+    const int bi = a.nbs - 1 - (int)(bid / (unsigned)a.Mg);
+    const int q = grid_model(a, bid % (unsigned)a.Mg);
     const int64_t q0 = a.queue_off[q];
     const int64_t N = a.queue_off[q + 1] - q0;
     const int bsz = a.bs[bi];
     const int64_t cap64 = a.rect ? N : (N < bsz ? N : (int64_t)bsz);
     if (cap64 <= 0 || cap64 > maxcap || cap64 > 64 * CR) return;   // the host sizes both
     const int ncap = (int)cap64;
-    // This workgroup scores prefix lengths n0 + 1 .. n1 (steps n0 .. n1 - 1).
-    // A launch too small to fill the chip splits them into chunks: the
-    // steps before n0 only rebuild G (warm-up steps), with the same fma
-    // sequence, so every chunk gives the bits a single workgroup would.
-    const int CH = a.chunk > 0 ? a.chunk : ncap;
-    const int n0 = kc * CH;
-    if (n0 >= ncap) return;
-    const int n1 = min(ncap, n0 + CH);
     // The longest workgroups set a saturated launch's length (their steps
     // run one after another while shorter ones share their SIMD): they
     // take issue priority over the short ones, graded by their step count.
-    if (n1 - n0 >= 48) __builtin_amdgcn_s_setprio(3);
-    else if (n1 - n0 >= 32) __builtin_amdgcn_s_setprio(2);
-    else if (n1 - n0 >= 16) __builtin_amdgcn_s_setprio(1);
+    if (ncap >= 48) __builtin_amdgcn_s_setprio(3);
+    else if (ncap >= 32) __builtin_amdgcn_s_setprio(2);
+    else if (ncap >= 16) __builtin_amdgcn_s_setprio(1);
 
     // Affine mode (Eq. (3)): a batch of size s whose slowest member takes l
     // runs c0 + c1 s l, so its latency histogram is the base grid's with
@@ -747,7 +730,7 @@ __device__ __forceinline__ void score_wave(const ScoreArgs& a, const unsigned bi
     // rest.  The branch comes before any per-lane state, so the two versions
     // share no registers' worth of live values.  The last member's plan
     // gives its home panel, as it does below.
-    const int lastp = __builtin_amdgcn_readfirstlane((int)make_plan(n1 - 1, false).hp);
+    const int lastp = __builtin_amdgcn_readfirstlane((int)make_plan(ncap - 1, false).hp);
     auto rest = [&](auto one_tag) {
         constexpr bool ONE = decltype(one_tag)::value;
         // The prologue is a chain of memory round trips, which the launches too
@@ -780,12 +763,12 @@ __device__ __forceinline__ void score_wave(const ScoreArgs& a, const unsigned bi
 #pragma unroll
         for (int r = 0; r < CR; ++r) {
             const int m = r * 64 + lane;
-            int c = a.cls[q0 + min(m, n1 - 1)];
+            int c = a.cls[q0 + min(m, ncap - 1)];
             if (c < 0 || c >= a.C) c = 0;                     // flagged by its plan
             cls_r.v[r] = __builtin_bit_cast(float, c);
             lo_r.v[r] = __builtin_bit_cast(float, sup_qb ? sup_qb[2 * c] : 0);
             hi_r.v[r] = __builtin_bit_cast(float, sup_qb ? sup_qb[2 * c + 1] : K);
-            if (m < n1) s_mem[m] = make_plan(m, true);
+            if (m < ncap) s_mem[m] = make_plan(m, true);
         }
         if (lane == 0) {
             s_kd[0] = 0.0;
@@ -800,17 +783,17 @@ __device__ __forceinline__ void score_wave(const ScoreArgs& a, const unsigned bi
         // The main loop walks the panels up to LASTP; the tabulated mode then
         // sums the rest (E-only panels) in a loop of its own, the affine mode
         // takes them from emax_kernel.
-        const int LASTP = ONE ? 0 : __builtin_amdgcn_readfirstlane((int)s_mem[n1 - 1].hp);
+        const int LASTP = ONE ? 0 : __builtin_amdgcn_readfirstlane((int)s_mem[ncap - 1].hp);
         const int NPW = LASTP + 1;
         // first member of each panel p in lane p (home panels are non-decreasing
         // in m): counted up to LASTP; every member's home panel lies before the
-        // later ones, so their lanes hold n1
-        int mlo_r = n1;
+        // later ones, so their lanes hold ncap
+        int mlo_r = ncap;
         for (int p = 0; p <= LASTP; ++p) {
             int cnt = 0;
-            for (int m0 = 0; m0 < n1; m0 += 64) {
+            for (int m0 = 0; m0 < ncap; m0 += 64) {
                 const int m = m0 + lane;
-                const bool below = m < n1 && s_mem[m].hp < p;
+                const bool below = m < ncap && s_mem[m].hp < p;
                 cnt += __builtin_popcountll(__ballot(below));
             }
             mlo_r = lane == p ? cnt : mlo_r;
@@ -865,33 +848,27 @@ __device__ __forceinline__ void score_wave(const ScoreArgs& a, const unsigned bi
         LaneCarry64<CR> cE, cP, cGl;
         cW.zero(); cGl.zero(); cN.zero(); cE.zero(); cP.zero();
 
-        // One flat loop over (panel p, step n in [ns, n1)), n fastest, padded at
-        // the end to a multiple of PF with ghost iterations (p == NP) so that
-        // ring slot i always holds iteration it0 + i.  The row of iteration
-        // it + PF is loaded PF iterations ahead; (p, n) and the prefetch
-        // position advance by counting.  A chunk of a split launch rebuilds G
-        // over the steps before n0 (warm-up): in a loop of its own at each pass
-        // start when its E sums come from emax_kernel (WARM_LOOP: the loop's
-        // deeper ring costs registers, which the launches that fill the chip
-        // cannot spare), else as iterations of this loop that update G only.
-        constexpr bool WARM_LOOP = ESPLIT && !AFF;
-        const int ns = WARM_LOOP ? n0 : 0;
-        const int total = NPW * (n1 - ns);
+        // One flat loop over (panel p, step n), n fastest, padded at the end to
+        // a multiple of PF with ghost iterations (p == NP) so that ring slot i
+        // always holds iteration it0 + i.  The row of iteration it + PF is
+        // loaded PF iterations ahead; (p, n) and the prefetch position advance
+        // by counting.
+        const int total = NPW * ncap;
         const int iters = (total + PF - 1) / PF * PF;
         const int base = lane * CPL;
 
         double Gacc[CPL];
         float buf[PF][CPL];
         int slo[PF], shi[PF];                                 // the slots' support bounds
-        int pf_p = 0, pf_n = ns;                              // prefetch position
+        int pf_p = 0, pf_n = 0;                               // prefetch position
 #pragma unroll
         for (int i = 0; i < PF; ++i) {
             load_step(buf[i], pf_n, pf_p * PW + base, false, slo[i], shi[i]);
             // keep the priming loads in ring order, as the loop issues them
             __builtin_amdgcn_sched_barrier(0);
-            if (++pf_n == n1) { pf_n = ns; pf_p = min(pf_p + 1, NPW - 1); }
+            if (++pf_n == ncap) { pf_n = 0; pf_p = min(pf_p + 1, NPW - 1); }
         }
-        int p = 0, n = ns;
+        int p = 0, n = 0;
         int mlo = __builtin_amdgcn_readlane(mlo_r, 0);
         int mend = __builtin_amdgcn_readlane(mlo_r, 1);
         // Trivial steps.  Where a panel lies wholly past the last bin with mass
@@ -909,42 +886,6 @@ __device__ __forceinline__ void score_wave(const ScoreArgs& a, const unsigned bi
         float etot_prev = 0.0f, T_prev = 0.0f;
         double gl_prev = 0.0;
 
-        // Warm-up: G over steps 0 .. n0-1 of panel pp (the product only, the
-        // same fma per bin and step as a scored step, so the same bits; a step
-        // whose row cannot change G multiplies by an exact 0 or finds G = 0),
-        // with rows loaded PFW steps ahead: these steps are short and would
-        // otherwise wait on their loads.  Leaves pass_zero for the steps after.
-        constexpr int PFW = ORLOJ_WARMUP_PREFETCH;
-        auto warm_up = [&](int pp) {
-            const int p0w = pp * PW, pbw = p0w + base;
-            float wb[PFW][CPL];
-            int wlo[PFW], whi[PFW];
-            bool zero = false;                   // G == 0 over the panel
-#pragma unroll
-            for (int i = 0; i < PFW; ++i) {
-                load_step(wb[i], min(i, n0 - 1), pbw, false, wlo[i], whi[i]);
-                __builtin_amdgcn_sched_barrier(0);
-            }
-            for (int w0 = 0; w0 < n0; w0 += PFW) {
-#pragma unroll
-                for (int i = 0; i < PFW; ++i) {
-                    const int nw = w0 + i;
-                    if (nw < n0) {
-#pragma unroll
-                        for (int j = 0; j < CPL; ++j) {
-                            const float t = (EXACT || pbw + j < K) ? wb[i][j] : 0.0f;
-                            Gacc[j] = fma(-Gacc[j], (double)t, Gacc[j]);
-                        }
-                        zero = zero || min(p0w + PW, K) <= wlo[i];
-                    }
-#pragma unroll
-                    for (int j = 0; j < CPL; ++j) asm volatile("" : "+v"(Gacc[j])::"memory");
-                    load_step(wb[i], min(nw + PFW, n0 - 1), pbw, zero, wlo[i], whi[i]);
-                }
-            }
-            pass_zero = zero;
-        };
-
         static_assert(PF % 2 == 0, "steps are reduced in pairs");
         for (int it0 = 0; it0 < iters; it0 += PF) {
             // each scoring step's member sums (0 in lanes without a member) and
@@ -956,20 +897,17 @@ __device__ __forceinline__ void score_wave(const ScoreArgs& a, const unsigned bi
             for (int i = 0; i < PF; ++i) redP[i] = 0.0, redN[i] = 0.0f, red_n[i] = -1;
 #pragma unroll
             for (int i = 0; i < PF; ++i) {
-                if (n == ns) {
+                if (n == 0) {
                     // a real branch (the asm keeps it from becoming selects)
                     asm volatile("" ::: "memory");
 #pragma unroll
                     for (int j = 0; j < CPL; ++j) Gacc[j] = 1.0;
                     pass_zero = false;
-                    if constexpr (WARM_LOOP) {
-                        if (n0 > 0 && p < NPW) warm_up(p);
-                    }
                     if constexpr (CR == 1) {
                         // at most 64 members: lane l scores member mlo + l of this
                         // pass at every step, so its plan is read from LDS once
                         pass_valid = mlo + lane < mend;
-                        pass_mb = s_mem[min(mlo + lane, n1 - 1)];
+                        pass_mb = s_mem[min(mlo + lane, ncap - 1)];
                         pass_th = (double)pass_mb.theta + (double)pass_mb.thlo;
                         quarter_weights(pass_mb.rq, pass_wq);
                     }
@@ -980,13 +918,12 @@ __device__ __forceinline__ void score_wave(const ScoreArgs& a, const unsigned bi
                 const int lo_n = slo[i];
                 // members of this panel among the first n+1 (ONE: all of them)
                 const int mhi = ONE ? n + 1 : min(mend, n + 1);
-                const bool real = n >= n0;                    // else a warm-up step
-                const bool due = real && (ONE || mlo < mhi);  // some member is scored at this step
+                const bool due = ONE || mlo < mhi;            // some member is scored at this step
                 // G unchanged by this step (a panel past the row's support, or G
-                // already 0 on it): a warm-up step then does nothing, a scored
-                // step after the chunk's first reuses the previous step's sums
+                // already 0 on it): a step after the first reuses the previous
+                // step's sums
                 const bool unchanged = pass_zero || p0 >= hi_n;
-                const bool skip = p >= NPW || (real ? (n > n0 && unchanged && !due) : unchanged);
+                const bool skip = p >= NPW || (n > 0 && unchanged && !due);
                 // G <- G * F = G - G (1 - F), in fp64; per-quarter sums
                 double gs[Q::QW];
                 float zqv[Q::NQ];
@@ -999,7 +936,7 @@ __device__ __forceinline__ void score_wave(const ScoreArgs& a, const unsigned bi
                             const int j = qq * Q::QW + r;
                             const float t = (EXACT || pbase + j < K) ? buf[i][j] : 0.0f;
                             Gacc[j] = fma(-Gacc[j], (double)t, Gacc[j]);
-                            if constexpr (!ESPLIT) gs[r] = qq == 0 ? Gacc[j] : gs[r] + Gacc[j];
+                            if constexpr (!AFF) gs[r] = qq == 0 ? Gacc[j] : gs[r] + Gacc[j];
                             zz = r == 0 ? Gacc[j] : fma(zz, d64, Gacc[j]);
                         }
                         zqv[qq] = (float)zz;
@@ -1013,8 +950,8 @@ __device__ __forceinline__ void score_wave(const ScoreArgs& a, const unsigned bi
                 // G == 0 over the pass from here on: later steps of it need no row
                 const bool zero_after = pass_zero || min(p0 + PW, K) <= lo_n;
                 load_step(buf[i], pf_n, pf_p * PW + base, zero_after && pf_p == p, slo[i], shi[i]);
-                if (++pf_n == n1) { pf_n = ns; pf_p = ONE ? 0 : min(pf_p + 1, NPW - 1); }
-                if (p < NPW && real) {                        // else a ghost or warm-up iteration
+                if (++pf_n == ncap) { pf_n = 0; pf_p = ONE ? 0 : min(pf_p + 1, NPW - 1); }
+                if (p < NPW) {                                // else a ghost iteration
                     float etot = etot_prev, T = T_prev;
                     double glast_here = gl_prev;
                     // carries in from the previous panel pass (zero in the first)
@@ -1041,7 +978,7 @@ __device__ __forceinline__ void score_wave(const ScoreArgs& a, const unsigned bi
                         }
                     }
                     if (!skip) {
-                        if constexpr (!ESPLIT) {
+                        if constexpr (!AFF) {
                             double gsum = gs[0];
 #pragma unroll
                             for (int r = 1; r < Q::QW; ++r) gsum += gs[r];
@@ -1146,11 +1083,11 @@ __device__ __forceinline__ void score_wave(const ScoreArgs& a, const unsigned bi
                         cW.set(n, fmaf(Win, dPW, T));
                         cGl.set(n, glast_here);
                     }
-                    if constexpr (!ESPLIT) cE.add(n, (double)etot);
+                    if constexpr (!AFF) cE.add(n, (double)etot);
                 }
                 pass_zero = zero_after;
-                if (++n == n1) {
-                    n = ns;
+                if (++n == ncap) {
+                    n = 0;
                     ++p;
                     if (!ONE) {
                         mlo = __builtin_amdgcn_readlane(mlo_r, min(p, NP));
@@ -1182,9 +1119,9 @@ __device__ __forceinline__ void score_wave(const ScoreArgs& a, const unsigned bi
         // these panels only add their sums of 1 - G to E[L_B], in a loop of its
         // own: the product and the sum, no discounted prefix, snapshot or
         // carries.  Its ring is primed afresh; the panels' sums are added in
-        // panel order after those of the member panels, as before.  (ESPLIT:
+        // panel order after those of the member panels, as before.  (AFF:
         // every panel's sums come from emax_kernel.)
-        if constexpr (!ESPLIT) {
+        if constexpr (!AFF) {
             if (LASTP + 1 < NP) {
                 constexpr int PFB = ORLOJ_EONLY_PREFETCH;   // its ring is deeper: fewer registers live here
                 // Classes repeat along a deadline-ordered queue (fast classes
@@ -1217,14 +1154,14 @@ __device__ __forceinline__ void score_wave(const ScoreArgs& a, const unsigned bi
                 // RC), NC + 1 + k (the first member of class k)
                 int rk_r = NC;
                 if constexpr (NC > 0) {
-                    const int cl = lane < n1 ? __builtin_bit_cast(int, cls_r.v[0]) : -1 - lane;
+                    const int cl = lane < ncap ? __builtin_bit_cast(int, cls_r.v[0]) : -1 - lane;
                     int cnt = 0, first = 64;        // members with this lane's class, the first of them
-                    for (int m = n1 - 1; m >= 0; --m) {
+                    for (int m = ncap - 1; m >= 0; --m) {
                         const bool same = __builtin_amdgcn_readlane(cl, m) == cl;
                         cnt += same ? 1 : 0;
                         first = same ? m : first;
                     }
-                    bool taken = lane >= n1;
+                    bool taken = lane >= ncap;
 #pragma unroll
                     for (int k = 0; k < NC; ++k) {
                         // most members first, ties to the earlier member; a
@@ -1260,14 +1197,14 @@ __device__ __forceinline__ void score_wave(const ScoreArgs& a, const unsigned bi
                     for (int j = 0; j < CPL; ++j) creg[k][j] = 0.0f;
                 float bufb[PFB][CPL];
                 int blo[PFB], bhi[PFB];
-                const int totalB = (NP - LASTP - 1) * n1;
+                const int totalB = (NP - LASTP - 1) * ncap;
                 const int itersB = (totalB + PFB - 1) / PFB * PFB;
                 int qf_p = LASTP + 1, qf_n = 0;
 #pragma unroll
                 for (int i = 0; i < PFB; ++i) {
                     load_e(bufb[i], qf_n, qf_p * PW + base, false, blo[i], bhi[i]);
                     __builtin_amdgcn_sched_barrier(0);
-                    if (++qf_n == n1) { qf_n = 0; qf_p = min(qf_p + 1, NP - 1); }
+                    if (++qf_n == ncap) { qf_n = 0; qf_p = min(qf_p + 1, NP - 1); }
                 }
                 int pb = LASTP + 1, nb = 0;
                 bool zero_b = false;
@@ -1285,9 +1222,8 @@ __device__ __forceinline__ void score_wave(const ScoreArgs& a, const unsigned bi
                         }
                         const int hi_n = bhi[i];
                         const int lo_n = blo[i];
-                        const bool real = nb >= n0;
                         const bool unchanged = zero_b || p0 >= hi_n;
-                        const bool skip = pb >= NP || (real ? (nb > n0 && unchanged) : unchanged);
+                        const bool skip = pb >= NP || (nb > 0 && unchanged);
                         double gs[Q::QW];
                         // G <- G (1 - t) over the lane's bins, t from the row
                         // slice (ring slot or cache register)
@@ -1351,8 +1287,8 @@ __device__ __forceinline__ void score_wave(const ScoreArgs& a, const unsigned bi
                         for (int j = 0; j < CPL; ++j) asm volatile("" : "+v"(Gacc[j])::"memory");
                         const bool zero_after = zero_b || min(p0 + PW, K) <= lo_n;
                         load_e(bufb[i], qf_n, qf_p * PW + base, zero_after && qf_p == pb, blo[i], bhi[i]);
-                        if (++qf_n == n1) { qf_n = 0; qf_p = min(qf_p + 1, NP - 1); }
-                        if (pb < NP && real) {
+                        if (++qf_n == ncap) { qf_n = 0; qf_p = min(qf_p + 1, NP - 1); }
+                        if (pb < NP) {
                             float etot = eprev;
                             if (!skip) {
                                 double gsum = gs[0];
@@ -1365,7 +1301,7 @@ __device__ __forceinline__ void score_wave(const ScoreArgs& a, const unsigned bi
                             cE.add(nb, (double)etot);
                         }
                         zero_b = zero_after;
-                        if (++nb == n1) { nb = 0; ++pb; }
+                        if (++nb == ncap) { nb = 0; ++pb; }
                     }
                 }
             }
@@ -1375,26 +1311,26 @@ __device__ __forceinline__ void score_wave(const ScoreArgs& a, const unsigned bi
 #pragma unroll
         for (int r = 0; r < CR; ++r) {
             const int n = r * 64 + lane;
-            if (n >= n0 && n < n1) {
+            if (n < ncap) {
                 double esum = cE.mine(r);
-                if (ESPLIT && !a.defer) {
+                if constexpr (AFF) {
                     // the panels' sums in panel order, as this kernel adds them
                     esum = 0.0;
-                    const size_t pair = AFF ? (size_t)q : (size_t)q * (size_t)a.nbs + (size_t)bi;
-                    const float* ps = a.psum + pair * (size_t)a.np_e * (size_t)maxcap + n;
+                    const float* ps = a.psum + (size_t)q * (size_t)a.np_e * (size_t)maxcap + n;
                     for (int pp = 0; pp < a.np_e; ++pp) esum += (double)ps[(size_t)pp * (size_t)maxcap];
                 }
                 a.E[cand + n] = cP.mine(r);
-                if (ESPLIT && a.defer) {
-                    // the selection finishes E[L_B] and the score from the
-                    // panel sums (same expression, same bits): it runs after
-                    // emax_kernel's waves, which share this launch
-                    a.S[cand + n] = cN.mine(r);
-                } else {
-                    const double el = c0q + w * (0.5 + esum);
-                    a.EL[cand + n] = (float)el;
-                    a.S[cand + n] = (float)((double)cN.mine(r) / el);
+                double c0e = c0q, we = w;
+                if constexpr (AFF) {
+                    // read again: kept through the step loop they cost spills
+                    const double *pc0 = a.c0, *pc1 = a.c1, *pw = a.width;
+                    asm volatile("" : "+s"(pc0), "+s"(pc1), "+s"(pw));
+                    c0e = pc0[q];
+                    we = pc1[q] * (double)bsz * pw[q];
                 }
+                const double el = c0e + we * (0.5 + esum);
+                a.EL[cand + n] = (float)el;
+                a.S[cand + n] = (float)((double)cN.mine(r) / el);
             }
         }
     };
@@ -1406,28 +1342,22 @@ __device__ __forceinline__ void score_wave(const ScoreArgs& a, const unsigned bi
 // waves per SIMD instead of the four their 100 would allow: the spills that
 // costs lie outside the step loop (cfg5 affine call 0.0788 -> 0.0738 ms; at
 // 72 VGPRs the loop spills and it takes 0.0856 ms).
-template <int CPL, int PF, bool EXACT, int CR, bool AFF, bool ESPLIT>
+template <int CPL, int PF, bool EXACT, int CR, bool AFF>
 __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(AFF && CR == 1 ? 6 : 1)))
 void score_kernel(const ScoreArgs a) {
-    score_wave<CPL, PF, EXACT, CR, AFF, ESPLIT>(a, blockIdx.x);
+    score_wave<CPL, PF, EXACT, CR, AFF>(a, blockIdx.x);
 }
 
 // ---------------------------------------------------------------------------
-// emax_kernel: the sums behind E[L_B], one wave per (pair, panel), ahead of
-// score_kernel.  E[L_B] = w (1/2 + sum_k (1 - G_n(x_{k+1}))) (Eq. (5)) needs
-// the panel sums of 1 - G for every prefix length n.  A wave keeps the
-// running product of its panel's bins over the pair's prefixes and writes
-// each step's panel sum to psum[(pair * panels + p) * maxcap + n], rounded
-// as score_kernel rounds its own per-panel sums, so E[L_B] has the same
-// bits either way.
-//   Affine mode: a pair is a model.  Under Eq. (3) every batch size's
-//     histogram is the same product G_n of the members' solo CDFs on the
-//     base grid, mapped onto a wider grid, so E[max] needs one product per
-//     prefix length, not one per batch size (c0 + c1 s E[max]).
-//   Tabulated mode, in launches split into step chunks: a pair is a (model,
-//     batch size).  The panels past every member's deadline then need no
-//     chunk to repeat their products: the score waves walk only the
-//     panels that hold members.
+// emax_kernel (affine mode): the sums behind E[L_B], one wave per (model,
+// panel), ahead of score_kernel.  E[L_B] = c0 + c1 s w (1/2 + sum_k
+// (1 - G_n(x_{k+1}))) (Eq. (5)) needs the panel sums of 1 - G for every
+// prefix length n.  Under Eq. (3) every batch size's histogram is the same
+// product G_n of the members' solo CDFs on the base grid, mapped onto a wider
+// grid, so they are formed once per prefix length, not once per batch size.
+// A wave keeps the running product of its panel's bins over the model's
+// prefixes and writes each step's panel sum to psum[(model * panels + p) *
+// maxcap + n], rounded to fp32 once.
 // Rows are loaded PFE steps ahead; the class and support of step n sit in
 // lane n % 64, so a step's row address needs no memory round trip.
 // ---------------------------------------------------------------------------
@@ -1438,7 +1368,7 @@ void score_kernel(const ScoreArgs a) {
 #define ORLOJ_EMAX_PREFETCH_OF(CPL) ((CPL) >= 16 ? 8 : (CPL) >= 8 ? 16 : 32)
 #endif
 
-template <int CPL, bool EXACT, int CR, bool AFF>
+template <int CPL, bool EXACT, int CR>
 __device__ __forceinline__ void emax_wave(const ScoreArgs& a, const unsigned bid) {
     using Q = Quarters<CPL>;
     constexpr int PW = 64 * CPL;
@@ -1448,17 +1378,9 @@ __device__ __forceinline__ void emax_wave(const ScoreArgs& a, const unsigned bid
     const int NP = (K + PW - 1) / PW;
     const unsigned pair = bid / (unsigned)NP;
     const int p = (int)(bid - pair * (unsigned)NP);
-    int q, bi;
-    size_t qb;                                  // the pair's rows and sums
-    if constexpr (AFF) {
-        q = grid_model(a, pair);
-        bi = a.nbs - 1;                         // the longest prefix (batch sizes increase)
-        qb = (size_t)q;
-    } else {
-        bi = a.nbs - 1 - (int)(pair / (unsigned)a.Mg);   // largest batch sizes first
-        q = grid_model(a, pair % (unsigned)a.Mg);
-        qb = (size_t)q * (size_t)a.nbs + (size_t)bi;
-    }
+    const int q = grid_model(a, pair);
+    const int bi = a.nbs - 1;                   // the longest prefix (batch sizes increase)
+    const size_t qb = (size_t)q;                // the model's rows and sums
     const int64_t q0 = a.queue_off[q];
     const int64_t N = a.queue_off[q + 1] - q0;
     const int64_t cap64 = a.rect ? N : (N < a.bs[bi] ? N : (int64_t)a.bs[bi]);
@@ -1506,10 +1428,8 @@ __device__ __forceinline__ void emax_wave(const ScoreArgs& a, const unsigned bid
         __builtin_amdgcn_sched_barrier(0);
     }
     // Each step's lane sums are parked in LDS, one row per step, and every
-    // 64 steps lane r adds up row r in the pairwise order in which the wave
-    // scan of score_kernel reaches its last lane (pairs of neighbouring
-    // lanes, then pairs of those, ...), so the panel sums have that
-    // kernel's bits without a cross-lane reduction on every step.
+    // 64 steps lane r adds up row r, pairwise: no cross-lane reduction on
+    // every step.
     __shared__ float s_e[64][65];
     for (int n0 = 0; n0 < ncap; n0 += PFE) {
 #pragma unroll
@@ -1559,23 +1479,746 @@ __device__ __forceinline__ void emax_wave(const ScoreArgs& a, const unsigned bid
     }
 }
 
-template <int CPL, bool EXACT, int CR, bool AFF>
+template <int CPL, bool EXACT, int CR>
 __global__ __launch_bounds__(64) void emax_kernel(const ScoreArgs a) {
-    emax_wave<CPL, EXACT, CR, AFF>(a, blockIdx.x);
+    emax_wave<CPL, EXACT, CR>(a, blockIdx.x);
 }
 
-// One launch for a scheduling round's tabulated scoring when the E sums come
-// from emax_kernel's waves: workgroups [0, n_emax) are those waves, the rest
-// score_kernel's (their E[L_B] and scores are finished by the selection,
-// which runs after the launch).  Nothing in the launch waits on anything
-// else in it, so the two kinds of waves run side by side.
-template <int CPL, bool EXACT, int CR>
-__global__ __launch_bounds__(64) void round_kernel(const ScoreArgs a, const unsigned n_emax) {
-    if (blockIdx.x < n_emax) {
-        emax_wave<CPL, EXACT, CR, false>(a, blockIdx.x);
-    } else {
-        score_wave<CPL, ORLOJ_SPLIT_PREFETCH, EXACT, CR, false, true>(a, blockIdx.x - n_emax);
+// ---------------------------------------------------------------------------
+// turned_kernel: scoring in launches too small to fill the chip.
+//
+// There score_kernel's waves, one per (model, batch size), run their steps
+// one after another with most of the chip idle.  Here a workgroup of up to
+// eight waves takes a block of 64 prefix lengths of one (model, batch size)
+// and its waves split the bins:
+//
+//   Member segments.  The bins up to the last deadline lie in equal segments,
+//   a wave each.  The wave forms G transposed, a block of 16 S bins
+//   x 16 RG prefix lengths (S RG = 4) at a time: a DPP row of 16 lanes takes
+//   16 members at 16 bins, their products are chained over the groups of 16
+//   members and turned in LDS, so that a lane holds one prefix length over
+//   16 consecutive bins.  The discounted prefix of Eq. (2) and the sums
+//   behind E[L_B] are then recurrences in a register, and a member's P and
+//   priority for all 64 prefix lengths take one evaluation with uniform
+//   constants: nothing is reduced over the lanes, and the sums over the
+//   members are the lanes' own.  S = 4 or 2 for prefixes of at most 16 or 32
+//   members, which would leave lanes idle otherwise.  The rows of a block are
+//   loaded while the block before it is worked on.
+//
+//   The discounted prefix carried into a segment is known only when the
+//   segments before it are done.  Every term of a priority is affine in it,
+//   so a segment runs from 0 and keeps the sum of the coefficients; the
+//   segments are joined at the end, in order.
+//
+//   The tiles past every member's deadline only add their sums of 1 - G to
+//   E[L_B] (TurnedWave::e_tile): lanes hold the bins, the steps run in order
+//   and each step's lane sums are added up eight steps at a time from LDS.
+//   The waves take these tiles from a shared counter.
+//
+// What bounds it: latency.  A member's evaluation is ~300 cycles and a block
+// of bins ~2500 on a wave that has its SIMD nearly to itself, which is why
+// the segments cut the member region evenly.  Score + selection, us, against
+// score_kernel in step chunks, the way taken before: 1 model of 128 bins and
+// prefixes to 16 15.8 -> 14.7; 1024 bins, to 64 33.1 -> 19.5; 2048 bins, to
+// 128 146 -> 57; 5 models, 1501 bins, every prefix to 100 152 -> 39.
+//
+// G is an fp64 product.  Within a group of 16 members it is chained from 1,
+// then multiplied by the product of the groups before: a member whose 1 - F
+// is 0 leaves every bit of it unchanged, so exact ties between prefixes stay
+// ties.  The segments depend on the queue and the batch size alone, and E's
+// sums over a segment or tile are rounded to multiples of 2^-40 before they
+// are added (any order gives the same sum), so the results depend on neither
+// the other models of the launch nor which wave takes which tile.
+// ---------------------------------------------------------------------------
+constexpr int kTurnWaves = 8;                   // waves of a workgroup
+constexpr int kETile = 128;                     // bins of an E tile: two per lane
+constexpr int kPanel = 256;                     // bins of one affine E sum
+constexpr int kGtRow = 136;                     // bytes of a turned row: 16 fp64, padded
+constexpr int kERow = 640;                      // bytes of a row of lane sums: 64 fp64, padded
+constexpr int kTriBytes = 64 * 65 / 2 * 4;      // a block's P when no prefix is longer than 64
+
+struct TurnedArgs {
+    const float* tab;          // [M][nbs][C][K] 1 - F(x_{k+1}); affine mode: [M][C][K]
+    const int64_t* queue_off;  // [M+1]
+    const int32_t* cls;        // [N]
+    const double* deadline;    // [N]
+    const double* now;         // [M]
+    const double* width;       // [M]
+    const int64_t* cand_off;   // [M+1]
+    const int64_t* prob_off;   // [M+1]
+    float* P;
+    double* E;
+    float* EL;
+    float* S;
+    const int32_t* sup;        // [M][nbs][C][2] first / last bin with mass, or NULL
+    const double* cost;        // [N] miss cost per request, or NULL (1)
+    const double* c0;          // affine mode: [M] fixed batch overhead (ms); else NULL
+    const double* c1;          // affine mode: [M] per-member slope
+    double* esum;              // affine mode: [M][np_e][maxcap] sums of 1 - G over kPanel bins
+    int np_e;
+    int* err;
+    double b;
+    int C, K, nbs, rect, maxcap;
+    int Mg;                    // models the grid covers: all, or the listed ones
+    int compact;               // 1: grid model i is act[i]
+    int nblk;                  // workgroups per (model, batch size): blocks of 64 prefix lengths
+    int bs[ORLOJ_MAX_BATCH_SIZES];
+    int act[kMaxActive];       // the models with a non-empty queue (compact)
+};
+
+// A kernel's only argument, read where the launch put it: by value, the
+// compiler copied its arrays to every lane's scratch memory (2.2 KB a lane).
+template <class T>
+__device__ __forceinline__ const T& kernel_args() {
+    return *(const T*)__builtin_amdgcn_kernarg_segment_ptr();
+}
+
+// LDS, byte offsets: the waves' areas (the turned block, or rows of lane
+// sums, per-step totals and the list of active steps), the plans, staged P
+// (up to 64 prefix lengths) and the tile counter.
+struct TurnedLds {
+    int wave, tot, list, plan, pst, ctrl, total;
+};
+
+__host__ __device__ constexpr TurnedLds turned_lds(int R, int W) {
+    TurnedLds l{};
+    l.tot = 8 * kERow;
+    l.list = l.tot + 512;
+    l.wave = 64 * kGtRow;
+    l.plan = W * l.wave;
+    l.pst = l.plan + 64 * R * 32;
+    l.ctrl = l.pst + (R == 1 ? kTriBytes : 0);
+    l.total = l.ctrl + 16;
+    return l;
+}
+static_assert(8 * kERow + 512 + 256 <= 64 * kGtRow, "rows of lane sums, totals, list");
+// at the end the segments' sums and the waves' E sums take the areas' place
+static_assert(2560 + 512 <= turned_lds(1, 1).wave, "a segment a wave");
+
+extern __shared__ __align__(16) unsigned char turned_smem[];
+
+template <class T>
+__device__ __forceinline__ T& lds_at(int off) {
+    return *reinterpret_cast<T*>(turned_smem + off);
+}
+
+template <int... J, class F>
+__device__ __forceinline__ void unroll_seq(std::integer_sequence<int, J...>, F&& f) {
+    (f(std::integral_constant<int, J>{}), ...);
+}
+template <int N, class F>
+__device__ __forceinline__ void unroll(F&& f) {
+    unroll_seq(std::make_integer_sequence<int, N>{}, f);
+}
+
+// Lane J of each row of 16 lanes, in every lane of the row.
+template <int J>
+__device__ __forceinline__ unsigned row_bcast(unsigned x) {
+    return (unsigned)__builtin_amdgcn_update_dpp(0, (int)x, 0x150 + J, 0xf, 0xf, true);
+}
+
+// Sum over the wave (a scalar).
+template <int CTRL, int ROWMASK = 0xf>
+__device__ __forceinline__ int dpp_i32(int x) {
+    return __builtin_amdgcn_update_dpp(0, x, CTRL, ROWMASK, 0xf, true);
+}
+__device__ __forceinline__ int wave_sum_i32(int x) {
+    x += dpp_i32<0x111>(x);
+    x += dpp_i32<0x112>(x);
+    x += dpp_i32<0x114>(x);
+    x += dpp_i32<0x118>(x);
+    x += dpp_i32<0x142, 0xa>(x);
+    x += dpp_i32<0x143, 0xc>(x);
+    return __builtin_amdgcn_readlane(x, 63);
+}
+
+// x rounded to a multiple of 2^-40, for |x| < 2048: sums of such values
+// below 2^13 are exact in any order.
+__device__ __forceinline__ double round_e(double x) {
+    constexpr double kM = 6144.0;
+    return (x + kM) - kM;
+}
+
+__device__ __forceinline__ unsigned long long lanes_below(int lane) { return (1ull << lane) - 1ull; }
+
+// 1 - exp(-x) for x >= 0.  Every lane's x is small where a bin is short
+// against the anticipated delay (the usual case): a Taylor polynomial, whose
+// remainder is below 2^-57 of the value for x <= 1/64, instead of the
+// library's longer chain.
+__device__ __forceinline__ double one_minus_exp(double x) {
+    if (__all(x <= 0x1p-6)) {
+        double p = 1.0 / 40320.0;
+        p = fma(-x, p, 1.0 / 5040.0);
+        p = fma(-x, p, 1.0 / 720.0);
+        p = fma(-x, p, 1.0 / 120.0);
+        p = fma(-x, p, 1.0 / 24.0);
+        p = fma(-x, p, 1.0 / 6.0);
+        p = fma(-x, p, 0.5);
+        p = fma(-x, p, 1.0);
+        return x * p;
     }
+    return -expm1(-x);
+}
+
+// One wave's members: member m in lane m % 64 of register m / 64.
+template <int R>
+struct TurnedWave {
+    const unsigned char* tab;  // the rows of this (model, batch size)
+    int K, lane, n1, blk;      // members, and the block of prefix lengths scored
+    int area;                  // this wave's LDS
+    TurnedLds l;
+    unsigned co[R];            // byte offset of the member's row
+    int lo[R], hi[R];          // its support
+
+    __device__ __forceinline__ float row_at(unsigned off) const {
+        return *reinterpret_cast<const float*>(tab + off);
+    }
+
+    __device__ __forceinline__ void load_members(const TurnedArgs& a, int64_t q0, const int32_t* sup_qb) {
+#pragma unroll
+        for (int r = 0; r < R; ++r) {
+            co[r] = 0;
+            lo[r] = 0;
+            hi[r] = K;
+            if (r <= blk) {
+                const int m = 64 * r + lane;
+                int c = m < n1 ? a.cls[q0 + m] : 0;
+                if (c < 0 || c >= a.C) c = 0;             // flagged with the member's bin
+                co[r] = 4u * (unsigned)c * (unsigned)K;
+                if (sup_qb) {
+                    lo[r] = sup_qb[2 * (size_t)c];
+                    hi[r] = sup_qb[2 * (size_t)c + 1];
+                }
+            }
+        }
+    }
+
+    // Sum of G over the valid bins of the kETile bins from tile0 on, prefix
+    // length 64 blk + lane + 1.  Rows whose support misses the tile are not
+    // read: past a row's last bin with mass 1 - F is exactly 0 (G is
+    // unchanged), before its first exactly 1 (G becomes 0), so the sums are
+    // the same bits with and without the support.
+    __device__ __forceinline__ double e_tile(int tile0) {
+        const int tend = min(tile0 + kETile, K);
+        const int b0 = tile0 + 2 * lane;
+        const unsigned o0 = 4u * (unsigned)min(b0, K - 1), o1 = 4u * (unsigned)min(b0 + 1, K - 1);
+        double G0 = b0 < K ? 1.0 : 0.0, G1 = b0 + 1 < K ? 1.0 : 0.0;
+        int nstop = 0x7fffffff;                            // first member wholly past the tile
+#pragma unroll
+        for (int r = 0; r < R; ++r) {
+            if (r <= blk) {
+                const unsigned long long mo = __ballot(64 * r + lane < n1 && tend <= lo[r]);
+                if (mo != 0ull) nstop = min(nstop, 64 * r + (int)__ffsll((long long)mo) - 1);
+            }
+        }
+        if (nstop < 64 * blk) return 0.0;
+        double before = (double)(tend - tile0);            // before the block's first active member
+        double sum = 0.0;
+#pragma unroll
+        for (int r = 0; r < R; ++r) {
+            if (r <= blk) {
+                // the active members of this register, in order
+                const int m = 64 * r + lane;
+                const bool act = m < n1 && m < nstop && hi[r] > tile0;
+                const unsigned long long mk = __ballot(act);
+                const int cnt = __popcll(mk), rk = __popcll(mk & lanes_below(lane));
+                if (act) lds_at<unsigned>(area + l.list + 4 * rk) = co[r];
+                wave_lds_fence();
+                const unsigned lv = cnt > 0 ? lds_at<unsigned>(area + l.list + 4 * min(lane, cnt - 1)) : 0u;
+                const bool rows = r == blk;
+                // the rows of the 16 steps after the eight worked on are on
+                // their way
+                float t[3][8][2];
+                auto load = [&](float (&v)[8][2], int g) {
+#pragma unroll
+                    for (int u = 0; u < 8; ++u) {
+                        const unsigned c = (unsigned)__builtin_amdgcn_readlane((int)lv, (g + u) & 63);
+                        v[u][0] = row_at(c + o0);
+                        v[u][1] = row_at(c + o1);
+                    }
+                };
+                load(t[0], 0);
+                load(t[1], 8);
+#pragma unroll 1
+                for (int g = 0; g < cnt; g += 8) {
+                    load(t[2], g + 16);
+#pragma unroll
+                    for (int u = 0; u < 8; ++u) {
+                        if (g + u < cnt) {
+                            G0 = fma(-G0, (double)t[0][u][0], G0);
+                            G1 = fma(-G1, (double)t[0][u][1], G1);
+                        }
+                        if (rows) lds_at<double>(area + u * kERow + 8 * lane) = G0 + G1;
+                    }
+                    if (rows) add_rows(g);
+#pragma unroll
+                    for (int u = 0; u < 8; ++u)
+#pragma unroll
+                        for (int j = 0; j < 2; ++j) {
+                            t[0][u][j] = t[1][u][j];
+                            t[1][u][j] = t[2][u][j];
+                        }
+                }
+                if (r + 1 == blk) {
+                    // G of the block before: its sum, for the block's first prefixes
+                    lds_at<double>(area + 8 * lane) = G0 + G1;
+                    add_rows(0);
+                    before = lds_at<double>(area + l.tot);
+                }
+                if (rows) {
+                    const int last = rk + (act ? 1 : 0) - 1;   // the last active step up to this one
+                    sum = last >= 0 ? lds_at<double>(area + l.tot + 8 * last) : before;
+                    if (m >= nstop) sum = 0.0;
+                }
+                wave_lds_fence();
+            }
+        }
+        return sum;
+    }
+
+    // the sums over the lanes of eight rows, to the totals from t0 on
+    __device__ __forceinline__ void add_rows(int t0) {
+        wave_lds_fence();
+        const int row = lane >> 3, oct = lane & 7;         // eight lanes a row
+        double s = 0.0;
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+            const double2 v = lds_at<double2>(area + row * kERow + 16 * (8 * j + oct));
+            s = j == 0 ? v.x + v.y : s + (v.x + v.y);
+        }
+        s += dpp64<0xb1>(s);       // quad_perm 1 0 3 2
+        s += dpp64<0x4e>(s);       // quad_perm 2 3 0 1
+        s += dpp64<0x141>(s);      // row_half_mirror
+        if (oct == 0) lds_at<double>(area + l.tot + 8 * (t0 + row)) = s;
+        wave_lds_fence();
+    }
+};
+
+// A member's constants for Eq. (2), in LDS: read uniformly, one member ahead.
+struct alignas(16) Plan {
+    double th;      // position inside bin k
+    double A;       // cost (1 - d) exp(-b theta w), or cost (1 - d) exp(-b (tau - K w))
+    double Bc;      // cost (1 - exp(-b theta w))
+    double cc;      // A (1 - d) d^(k - the segment's first bin); 0 in the first segment
+};
+static_assert(sizeof(Plan) == 32, "plan size");
+
+template <int R, bool AFF>
+__device__ __forceinline__ void turned_block(const TurnedArgs& a) {
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int wv = __builtin_amdgcn_readfirstlane(tid >> 6);
+    constexpr int W = kTurnWaves;
+    const int K = a.K;
+    constexpr TurnedLds l = turned_lds(R, W);
+
+    const unsigned per_bs = (unsigned)a.Mg * (unsigned)a.nblk;
+    const int bi = a.nbs - 1 - (int)(blockIdx.x / per_bs);
+    const unsigned rem = blockIdx.x % per_bs;
+    const int blk = R > 1 ? a.nblk - 1 - (int)(rem / (unsigned)a.Mg) : 0;
+    const int q = a.compact ? a.act[rem % (unsigned)a.Mg] : (int)(rem % (unsigned)a.Mg);
+    const int64_t q0 = a.queue_off[q];
+    const int64_t N = a.queue_off[q + 1] - q0;
+    const int bsz = a.bs[bi];
+    int64_t cand = a.cand_off[q], prob = a.prob_off[q];
+    const int64_t cap64 = a.rect ? N : (N < bsz ? N : (int64_t)bsz);
+    if (cap64 <= 64 * blk || cap64 > a.maxcap || cap64 > 64 * R) return;   // the host sizes both
+    const int n1 = min((int)cap64, 64 * (blk + 1));        // members of the block's longest prefix
+    const int nb = n1 - 64 * blk;                          // prefix lengths of the block
+    const size_t qb = AFF ? (size_t)q : (size_t)q * (size_t)a.nbs + (size_t)bi;
+
+    TurnedWave<R> t;
+    t.tab = reinterpret_cast<const unsigned char*>(a.tab + qb * (size_t)a.C * (size_t)K);
+    t.K = K;
+    t.lane = lane;
+    t.n1 = n1;
+    t.blk = blk;
+    t.l = l;
+    t.area = wv * l.wave;
+    t.load_members(a, q0, a.sup ? a.sup + qb * (size_t)a.C * 2 : nullptr);
+    double tau[R], cost[R];
+#pragma unroll
+    for (int r = 0; r < R; ++r) {
+        const int m = 64 * r + lane;
+        const bool in = r <= blk && m < n1;
+        tau[r] = in ? a.deadline[q0 + m] : 0.0;
+        cost[r] = in && a.cost ? a.cost[q0 + m] : 1.0;
+    }
+
+    // Affine mode (Eq. (3)): a batch of size s whose slowest member takes l
+    // runs c0 + c1 s l: the bin width is c1 s w, the time left tau - c0, and
+    // E[L_B] = c0 + c1 s E[max] (Eq. (5)), whose sums come from
+    // turned_esum_kernel.  Tabulated mode: c0 = 0, width w.
+    const double wq = a.width[q];
+    double c0q = 0.0, w = wq;
+    bool aok = true;
+    if constexpr (AFF) {
+        c0q = a.c0[q];
+        const double c1 = a.c1[q];
+        aok = c0q >= 0.0 && c0q < HUGE_VAL && c1 > 0.0 && c1 < HUGE_VAL;
+        w = c1 * (double)bsz * wq;
+    }
+    const bool wok = wq > 0.0 && wq < HUGE_VAL && aok && w > 0.0 && w < HUGE_VAL;   // else a data error
+    const double nowq = a.now[q];
+    const double b = a.b, bw = b * w;
+
+    if (tid == 0) lds_at<int>(l.ctrl) = 0;                 // E tiles handed out
+    __syncthreads();
+
+    // ---- deadline bins: -1 dead, K beyond the grid
+    double th[R], left[R];                                 // position in the bin; time past its left edge
+    int kk[R];
+    int kmax = 0;
+#pragma unroll
+    for (int r = 0; r < R; ++r) {
+        kk[r] = -2;                                        // no member
+        th[r] = left[r] = 0.0;
+        if (r <= blk) {
+            const int m = 64 * r + lane;
+            if (m < n1) {
+                const double D = tau[r];
+                if (wv == W - 1) {
+                    // the member's data errors (once per workgroup)
+                    const int c = a.cls[q0 + m];
+                    int flag = 0;
+                    if (c < 0 || c >= a.C) flag |= kErrClassRange;
+                    if (isnan(D)) flag |= kErrDeadlineNaN;
+                    if (m > 0 && D < a.deadline[q0 + m - 1]) flag |= kErrUnsorted;
+                    if (m == 0 && isnan(nowq)) flag |= kErrNowNaN;
+                    if (m == 0 && !(wq > 0.0 && wq < HUGE_VAL)) flag |= kErrWidth;
+                    if (m == 0 && !aok) flag |= kErrAffine;
+                    if (!(cost[r] >= 0.0 && cost[r] < HUGE_VAL)) flag |= kErrCost;
+                    if (flag) atomicOr(a.err, flag);
+                }
+                kk[r] = -1;
+                const double ta = D - nowq - c0q;
+                if (ta > 0.0 && wok) {
+                    const double u = ta / w, uf = floor(u);
+                    if (u >= (double)K) {
+                        kk[r] = K;
+                        left[r] = ta - (double)K * w;
+                    } else {
+                        kk[r] = (int)uf;
+                        th[r] = u - uf;
+                        left[r] = th[r] * w;
+                    }
+                }
+                kmax = max(kmax, min(kk[r], K - 1));
+            }
+        }
+        if (!(cost[r] >= 0.0 && cost[r] < HUGE_VAL)) cost[r] = 0.0;
+    }
+    kmax = __builtin_amdgcn_readfirstlane(wave_max_i32(kmax));
+
+    // this batch size's block of candidates and member slots starts after
+    // those of the batch sizes before it
+    {
+        int dc = 0, dp = 0;                                // (caps are at most ORLOJ_MAX_PREFIX)
+        for (int j0 = 0; j0 < bi; j0 += 64) {
+            const int j = j0 + lane;
+            if (j < bi) {
+                const int c = (int)(a.rect ? N : (N < a.bs[j] ? N : (int64_t)a.bs[j]));
+                dc += c;
+                dp += c * (c + 1) / 2;
+            }
+        }
+        cand += wave_sum_i32(dc);
+        prob += wave_sum_i32(dp);
+    }
+
+    // lane (row, i) of a segment: prefix length nidx + 1, part `part` of a block
+    const int S = nb <= 16 ? 4 : nb <= 32 ? 2 : 1, RG = 4 / S;
+    const int row = lane >> 4, ri = lane & 15, part = row % S, grp = row / S;
+    const int nrel = 16 * grp + ri, nidx = nrel < nb ? 64 * blk + nrel : -1;
+    const int row0 = 16 * grp * S + ri;                    // the lane of part 0 of this prefix length
+    float* const Pn = a.P + prob + (int64_t)nidx * (nidx + 1) / 2;   // this prefix length's P (R > 1)
+    // the member region: blocks of 16 S bins up to the last deadline, the
+    // same number of them for each segment
+    const int nblocks = kmax / (16 * S) + 1, per = (nblocks + W - 1) / W;
+    const int Ls = per * 16 * S, kend0 = nblocks * 16 * S, lseg = (nblocks - 1) / per;
+    const double omd = one_minus_exp(bw), d = 1.0 - omd;
+    double accP = 0.0, accN = 0.0, accC = 0.0, es = 0.0;   // this wave's segment: sums of P, N, C and G
+    double Y = 0.0, gpc = 0.0;                             // discounted prefix and G before the block
+
+    // ---- member segments, one per wave
+    if (wv <= lseg) {
+        __builtin_amdgcn_s_setprio(3);                     // the others wait for these
+        const int k0 = wv * Ls, kend = min(k0 + Ls, kend0);
+        // The rows of a block of bins are loaded 16 members at a time per DPP
+        // row: passes over the members before this block of prefix lengths,
+        // then the block's own.  An item is one pass; the next item's rows
+        // are on their way while one is worked on.
+        const int passes = blk * S + 1;
+        float tv[16], tn[16];
+        auto issue = [&](int base, int p) {
+            unsigned c = t.co[0];
+#pragma unroll
+            for (int r = 1; r < R; ++r) c = p / S == r ? t.co[r] : c;
+            if (S > 1) c = (unsigned)__shfl((int)c, 16 * ((p % S) * RG + grp) + ri, 64);
+            // (the last entry of a row is 0: bins past the grid hold G = 1)
+            const unsigned o = 4u * (unsigned)min(base + 16 * part + ri, K - 1);
+            unroll<16>([&](auto j) { tn[decltype(j)::value] = t.row_at(row_bcast<decltype(j)::value>(c) + o); });
+        };
+        // the block before the segment only gives G at its last bin
+        int base = k0 - (wv > 0 ? 16 * S : 0), pass = 0;
+        issue(base, 0);
+
+        int me = 0, mb = 0;                                // its members
+#pragma unroll
+        for (int r = 0; r < R; ++r) {
+            const int k = min(max(kk[r], 0), K - 1);
+            me += __popcll(__ballot(kk[r] > -2 && k < k0));
+            mb += __popcll(__ballot(kk[r] > -2 && (k < k0 + Ls || wv == lseg)));
+        }
+        me = __builtin_amdgcn_readfirstlane(me);
+        mb = __builtin_amdgcn_readfirstlane(mb);
+        const double d2 = d * d, d4 = d2 * d2, d8 = d4 * d4, d16 = d8 * d8;
+        // its members' constants
+#pragma unroll 1
+        for (int r0 = me >> 6; 64 * r0 < mb; ++r0) {
+            Plan p;
+            double lf = left[0], cm = cost[0];
+            int k = kk[0];
+            p.th = th[0];
+#pragma unroll
+            for (int r = 1; r < R; ++r) {
+                lf = r0 == r ? left[r] : lf;
+                cm = r0 == r ? cost[r] : cm;
+                k = r0 == r ? kk[r] : k;
+                p.th = r0 == r ? th[r] : p.th;
+            }
+            const double m1 = one_minus_exp(b * lf);
+            double e1 = 1.0 - m1;
+            if (__any(e1 < 0.5)) e1 = exp(-b * lf);        // its own digits where it is small
+            p.A = k >= 0 ? cm * omd * e1 : 0.0;
+            p.Bc = k >= 0 && k < K ? cm * m1 : 0.0;
+            p.cc = 0.0;
+            if (k0 > 0) p.cc = p.A * omd * exp(-bw * (double)(k - k0));
+            const int m = 64 * r0 + lane;
+            if (m >= me && m < mb) lds_at<Plan>(l.plan + 32 * m) = p;
+        }
+        wave_lds_fence();
+        auto plan_of = [&](int m) -> const Plan& { return lds_at<Plan>(l.plan + 32 * min(m, n1 - 1)); };
+        Plan cur = plan_of(me), nxt = plan_of(me + 1);
+        auto bin_of = [&](int m) {
+            if (m >= mb) return 0x7fffffff;
+            int k = kk[0];
+#pragma unroll
+            for (int r = 1; r < R; ++r) k = (m >> 6) == r ? kk[r] : k;
+            return (int)__builtin_amdgcn_readlane(k, m & 63);
+        };
+        int ck = bin_of(me), cn = bin_of(me + 1);          // the next two members' bins
+        // member `me` at a bin with G = gp on its left edge, gc on its right
+        // one and discounted prefix y two bins before: for the lanes of part h
+        auto event = [&](double y, double gp, double gc, int h) {
+            if (nidx >= me && part == h) {
+                const double dg = gc - gp;
+                double P = fma(cur.th, dg, gp);
+                const double num = fma(cur.A, fma(-omd, y, gp), cur.Bc * dg);
+                P = ck >= 0 ? P : 0.0;                     // dead: its constants are 0 as well
+                accP += P;
+                accN += num;
+                accC += cur.cc;
+                if constexpr (R == 1) lds_at<float>(l.pst + 2 * nrel * (nrel + 1) + 4 * me) = (float)P;
+                else Pn[me] = (float)P;
+            }
+            ++me;
+            ck = cn;
+            cn = bin_of(me + 1);
+            cur = nxt;
+            nxt = plan_of(me + 1);
+        };
+        double Gs = 1.0;                                   // product of the members before
+        while (base < kend) {
+#pragma unroll
+            for (int j = 0; j < 16; ++j) tv[j] = tn[j];
+            const int pb = base, pp = pass;
+            if (++pass == passes) {
+                pass = 0;
+                base += 16 * S;
+            }
+            if (base < kend) issue(base, pass);
+            double Q[16];
+#pragma unroll
+            for (int j = 0; j < 16; ++j)
+                Q[j] = j == 0 ? 1.0 - (double)tv[0] : fma(-Q[j - 1], (double)tv[j], Q[j - 1]);
+            if (pp + 1 < passes) {
+                for (int h = 0; h < RG; ++h) Gs *= __shfl(Q[15], 16 * (h * S + part) + ri, 64);
+                continue;
+            }
+            for (int h = 0; h < RG - 1; ++h) {
+                const double x = __shfl(Q[15], 16 * (h * S + part) + ri, 64);
+                Gs = grp > h ? Gs * x : Gs;
+            }
+            // turned: lane (row, i) takes 16 bins of its prefix length
+            double g[16];
+            const int wr = t.area + 16 * row * kGtRow + 8 * ri, rd = t.area + lane * kGtRow;
+#pragma unroll
+            for (int j = 0; j < 16; ++j) lds_at<double>(wr + j * kGtRow) = Gs * Q[j];
+            wave_lds_fence();
+#pragma unroll
+            for (int j = 0; j < 16; ++j) g[j] = lds_at<double>(rd + 8 * j);
+            wave_lds_fence();
+            Gs = 1.0;
+            double gp0 = gpc;
+            if (S > 1) {
+                const double gl = __shfl(g[15], lane < 16 ? lane : lane - 16, 64);
+                gp0 = part == 0 ? gpc : gl;
+                gpc = __shfl(g[15], row0 + 16 * (S - 1), 64);
+            } else {
+                gpc = g[15];
+            }
+            if (pb < k0) continue;
+            double Ys = Y;
+            if (S > 1 || ck > pb + 15) {
+                // no member here, or several parts: the discounted prefix
+                // first, before each part and after the block
+                double y = 0.0, gp = gp0;
+#pragma unroll
+                for (int i = 0; i < 16; ++i) {
+                    y = fma(y, d, gp);
+                    gp = g[i];
+                    es += gp;
+                }
+                if (S > 1) {
+                    double Yr = Y;
+                    for (int h = 0; h < S; ++h) {
+                        Ys = part == h ? Yr : Ys;
+                        Yr = fma(Yr, d16, __shfl(y, row0 + 16 * h, 64));
+                    }
+                    Y = Yr;
+                } else {
+                    Y = fma(Y, d16, y);
+                }
+                if (ck > pb + 16 * S - 1) continue;
+            }
+            for (int h = 0; h < S; ++h) {
+                const int bh = pb + 16 * h;
+                if (ck > bh + 15) continue;
+                double y = Ys, gp = gp0;
+#pragma unroll
+                for (int i = 0; i < 16; ++i) {
+                    while (ck <= bh + i) event(y, gp, g[i], h);
+                    y = fma(y, d, gp);
+                    gp = g[i];
+                    if (S == 1) es += gp;
+                }
+                if (S == 1) Y = y;
+            }
+        }
+        // beyond the grid: at bin K (also whatever unsorted deadlines left over)
+        while (me < mb) event(Y, gpc, gpc, 0);
+        __builtin_amdgcn_s_setprio(0);
+    }
+
+    // ---- E tiles past the member region (tabulated mode); lane n: prefix
+    // length 64 blk + n + 1
+    double eacc = 0.0;
+    if constexpr (!AFF) {
+        for (;;) {
+            int T = 0;
+            if (lane == 0) T = atomicAdd(&lds_at<int>(l.ctrl), 1);
+            const int tile0 = kend0 + kETile * __builtin_amdgcn_readfirstlane(T);
+            if (tile0 >= K) break;
+            eacc += round_e((double)(min(tile0 + kETile, K) - tile0) - t.e_tile(tile0));
+        }
+    }
+
+    // ---- join the segments and the waves' E sums
+    double v[4] = {accP, accN, accC, es};
+    if (S > 1 && wv <= lseg) {
+#pragma unroll
+        for (int f = 0; f < 4; ++f) {
+            const double x = v[f];
+            v[f] = __shfl(x, row0, 64);
+            for (int h = 1; h < S; ++h) v[f] += __shfl(x, row0 + 16 * h, 64);
+        }
+    }
+    __syncthreads();
+    const int ework = 2560 * W;
+    if (!AFF) lds_at<double>(ework + 512 * wv + 8 * lane) = eacc;
+    if (wv <= lseg && part == 0) {
+        // 1 - G over the segment (bins past the grid hold G = 1)
+        v[3] = round_e((double)(min(wv * Ls + Ls, kend0) - wv * Ls) - v[3]);
+        const int at = 2560 * wv + 8 * nrel;
+#pragma unroll
+        for (int f = 0; f < 4; ++f) lds_at<double>(at + 512 * f) = v[f];
+        lds_at<double>(at + 2048) = Y;
+    }
+    if constexpr (R == 1) {
+        for (int i = tid; i < nb * (nb + 1) / 2; i += (int)blockDim.x) a.P[prob + i] = lds_at<float>(l.pst + 4 * i);
+    }
+    double dL = 0.0;
+    if (lseg > 0 && wv == 0) dL = exp(-bw * (double)Ls);
+    __syncthreads();
+    if (wv == 0 && lane < nb) {
+        // A priority's terms are A (gp - omd y) + Bc (gc - gp), over b w; the
+        // prefix carried into a segment adds cc / A of it to every omd y
+        double Yin = 0.0, P = 0.0, Nn = 0.0, E = 0.0;
+        for (int seg = 0; seg <= lseg; ++seg) {
+            const int at = 2560 * seg + 8 * lane;
+            P += lds_at<double>(at);
+            const double n0 = lds_at<double>(at + 512);
+            Nn += seg > 0 ? fma(-lds_at<double>(at + 1024), Yin, n0) : n0;
+            E += lds_at<double>(at + 1536);
+            Yin = fma(Yin, dL, lds_at<double>(at + 2048));
+        }
+        Nn = wok ? Nn / bw : 0.0;
+        const int n = 64 * blk + lane;
+        if constexpr (AFF) {
+            const double* ep = a.esum + (size_t)q * (size_t)a.np_e * (size_t)a.maxcap + n;
+            E = 0.0;
+            for (int p = 0; p < a.np_e; ++p) E += ep[(size_t)p * (size_t)a.maxcap];
+        } else {
+            for (int u = 0; u < W; ++u) E += lds_at<double>(ework + 512 * u + 8 * lane);
+        }
+        const double el = c0q + w * (0.5 + E);
+        a.E[cand + n] = P;
+        a.EL[cand + n] = (float)el;
+        a.S[cand + n] = (float)(Nn / el);
+    }
+}
+
+template <int R, bool AFF>
+__global__ __launch_bounds__(64 * kTurnWaves) void turned_kernel(const TurnedArgs) {
+    turned_block<R, AFF>(kernel_args<TurnedArgs>());
+}
+
+// The sums of 1 - G behind E[max] in the affine mode (see emax_kernel), for
+// turned_kernel: one workgroup of two waves per (model, kPanel bins, block
+// of prefix lengths).
+template <int R>
+__global__ __launch_bounds__(128) void turned_esum_kernel(const TurnedArgs) {
+    const TurnedArgs& a = kernel_args<TurnedArgs>();
+    const int lane = threadIdx.x & 63, wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const unsigned per = (unsigned)a.Mg * (unsigned)a.np_e;
+    const int blk = R > 1 ? a.nblk - 1 - (int)(blockIdx.x / per) : 0;
+    const unsigned rem = blockIdx.x % per;
+    const int q = a.compact ? a.act[rem / (unsigned)a.np_e] : (int)(rem / (unsigned)a.np_e);
+    const int p = (int)(rem % (unsigned)a.np_e);
+    const int64_t q0 = a.queue_off[q];
+    const int64_t N = a.queue_off[q + 1] - q0;
+    const int bsz = a.bs[a.nbs - 1];                       // the longest prefix (batch sizes increase)
+    const int64_t cap64 = a.rect ? N : (N < bsz ? N : (int64_t)bsz);
+    if (cap64 <= 64 * blk || cap64 > a.maxcap || cap64 > 64 * R) return;
+    TurnedWave<R> t;
+    t.tab = reinterpret_cast<const unsigned char*>(a.tab + (size_t)q * (size_t)a.C * (size_t)a.K);
+    t.K = a.K;
+    t.lane = lane;
+    t.n1 = min((int)cap64, 64 * (blk + 1));
+    t.blk = blk;
+    t.l = turned_lds(R, 2);
+    t.area = wv * t.l.wave;
+    t.load_members(a, q0, a.sup ? a.sup + (size_t)q * (size_t)a.C * 2 : nullptr);
+    static_assert(kPanel == 2 * kETile, "a tile per wave");
+    const int tile0 = p * kPanel + wv * kETile;
+    double e = 0.0;
+    if (tile0 < a.K) e = round_e((double)(min(tile0 + kETile, a.K) - tile0) - t.e_tile(tile0));
+    __syncthreads();
+    lds_at<double>(512 * wv + 8 * lane) = e;
+    __syncthreads();
+    const int n = 64 * blk + lane;
+    if (wv == 0 && n < t.n1)
+        a.esum[((size_t)q * (size_t)a.np_e + (size_t)p) * (size_t)a.maxcap + n] = e + lds_at<double>(512 + 8 * lane);
 }
 
 // ---------------------------------------------------------------------------
@@ -1586,21 +2229,13 @@ __global__ __launch_bounds__(64) void round_kernel(const ScoreArgs a, const unsi
 struct SelectArgs {
     const int64_t* queue_off;
     const int64_t* cand_off;
-    float* S;                  // read; written too when finishing
-    // finishing (a scheduling round whose score launch left it here): each
-    // candidate's E[L_B] and score from emax_kernel's panel sums and the
-    // priority sum the score waves wrote to S
-    int finish;
+    const float* S;
     // scheduling rounds (mapped host memory, or NULL): after its writes,
     // each workgroup g makes them visible to the host and writes `round`
     // to done[g], so the host can see the round finish without waiting for
     // the stream
     int32_t* done;
     int32_t round;
-    const float* psum;         // [M][nbs][np_e][maxcap]
-    int np_e, maxcap;
-    const double* width;       // [M]
-    float* EL;
     int32_t* sel_n;
     int32_t* sel_bs;
     float* sel_score;
@@ -1691,9 +2326,8 @@ __global__ __launch_bounds__(kSelThreads) void select_kernel(const SelectArgs a)
     // (batch size, n) from the block starts.  The comparison is a total
     // order, so the pick does not depend on the order of the visits.
     const int64_t total = s_start[a.nbs];
-    const double wq = a.finish ? a.width[q] : 0.0;
     for (int64_t i = tid; i < total; i += kSelThreads) {
-        float sc = S[i];
+        const float sc = S[i];
         int lo = 0, hi = a.nbs - 1;          // last bi with s_start[bi] <= i
         while (lo < hi) {
             const int mid = (lo + hi + 1) >> 1;
@@ -1701,18 +2335,6 @@ __global__ __launch_bounds__(kSelThreads) void select_kernel(const SelectArgs a)
         }
         const int n = (int)(i - s_start[lo]) + 1;
         const int bsz = a.bs[lo];
-        if (a.finish) {
-            // E[L_B] = w (1/2 + the panels' sums in panel order) and the
-            // score, as the score waves form them when they finish
-            const float* ps = a.psum + ((size_t)q * (size_t)a.nbs + (size_t)lo) * (size_t)a.np_e *
-                                           (size_t)a.maxcap + (size_t)(n - 1);
-            double esum = 0.0;
-            for (int pp = 0; pp < a.np_e; ++pp) esum += (double)ps[(size_t)pp * (size_t)a.maxcap];
-            const double el = 0.0 + wq * (0.5 + esum);
-            sc = (float)((double)sc / el);
-            a.EL[a.cand_off[q] + i] = (float)el;
-            a.S[a.cand_off[q] + i] = sc;
-        }
         if (n <= bsz && sc == sc)            // NaN never wins
             take_if_better(best, Best{sc, n, bsz});
     }
@@ -2511,22 +3133,18 @@ int chunk_per_lane(int K) {
 }
 
 
-template <int CPL, bool EXACT, int CR, bool AFF, bool ESPLIT>
+template <int CPL, bool EXACT, int CR, bool AFF>
 hipError_t launch_score_v(const ScoreArgs& a, unsigned grid, hipStream_t st) {
-    // the tabulated launches that take their E sums from emax_kernel are
-    // small ones (or split into chunks): few waves per SIMD to hide a row
-    // load's latency, so their ring is deeper
-    constexpr int PF = (ESPLIT && !AFF) ? ORLOJ_SPLIT_PREFETCH : ORLOJ_SCORE_PREFETCH;
+    constexpr int PF = ORLOJ_SCORE_PREFETCH;
     const size_t sm = score_fixed_bytes<CPL>() + (size_t)a.maxcap * score_bytes_per_member();
     static size_t attr_bytes = 0;   // per template instance; device-independent
     if (sm > attr_bytes) {
-        hipError_t e = hipFuncSetAttribute((const void*)score_kernel<CPL, PF, EXACT, CR, AFF, ESPLIT>,
+        hipError_t e = hipFuncSetAttribute((const void*)score_kernel<CPL, PF, EXACT, CR, AFF>,
                                            hipFuncAttributeMaxDynamicSharedMemorySize, (int)sm);
         if (e != hipSuccess) return e;
         attr_bytes = sm;
     }
-    hipLaunchKernelGGL((score_kernel<CPL, PF, EXACT, CR, AFF, ESPLIT>), dim3(grid), dim3(64), sm,
-                       st, a);
+    hipLaunchKernelGGL((score_kernel<CPL, PF, EXACT, CR, AFF>), dim3(grid), dim3(64), sm, st, a);
     return hipGetLastError();
 }
 
@@ -2562,76 +3180,70 @@ int score_chunk(int K) { return score_chunk_of(K); }
 
 // Step carries: one register per 64 steps (longest prefix up to 64, or up to
 // the compiled limit).
-template <int CPL, bool EXACT, bool AFF, bool ESPLIT>
+template <int CPL, bool EXACT, bool AFF>
 hipError_t launch_score_c(const ScoreArgs& a, unsigned grid, hipStream_t st) {
     constexpr int CRL = (ORLOJ_MAX_PREFIX + 63) / 64;
-    return a.maxcap <= 64 ? launch_score_v<CPL, EXACT, 1, AFF, ESPLIT>(a, grid, st)
-                          : launch_score_v<CPL, EXACT, CRL, AFF, ESPLIT>(a, grid, st);
+    return a.maxcap <= 64 ? launch_score_v<CPL, EXACT, 1, AFF>(a, grid, st)
+                          : launch_score_v<CPL, EXACT, CRL, AFF>(a, grid, st);
 }
 
-template <int CPL, bool AFF, bool ESPLIT>
+template <int CPL, bool AFF>
 hipError_t launch_score_m(const ScoreArgs& a, unsigned grid, hipStream_t st) {
-    return a.K % (64 * CPL) == 0 ? launch_score_c<CPL, true, AFF, ESPLIT>(a, grid, st)
-                                 : launch_score_c<CPL, false, AFF, ESPLIT>(a, grid, st);
+    return a.K % (64 * CPL) == 0 ? launch_score_c<CPL, true, AFF>(a, grid, st)
+                                 : launch_score_c<CPL, false, AFF>(a, grid, st);
 }
 
-// Affine mode: E sums from emax_kernel.  Tabulated mode: from emax_kernel
-// when the launch is split into step chunks over rows of more than two
-// panels (a.psum set), else summed by the score waves themselves.
 template <int CPL>
 hipError_t launch_score(const ScoreArgs& a, unsigned grid, hipStream_t st) {
-    if (a.c1) return launch_score_m<CPL, true, true>(a, grid, st);
-    return a.psum ? launch_score_m<CPL, false, true>(a, grid, st)
-                  : launch_score_m<CPL, false, false>(a, grid, st);
+    return a.c1 ? launch_score_m<CPL, true>(a, grid, st) : launch_score_m<CPL, false>(a, grid, st);
 }
 
-// emax_kernel: the tabulated kernel's panel width, so that its per-panel
-// sums round as that kernel's do.  One wave per (pair, panel): pairs are
-// models in the affine mode, (model, batch size) pairs in the tabulated one.
-template <int CPL, bool AFF>
-hipError_t launch_emax_m(const ScoreArgs& a, hipStream_t st) {
-    const unsigned pairs = AFF ? (unsigned)a.Mg : (unsigned)a.Mg * (unsigned)a.nbs;
-    const unsigned g = pairs * (unsigned)a.np_e;
+// emax_kernel: one wave per (model, panel).
+template <int CPL>
+hipError_t launch_emax(const ScoreArgs& a, hipStream_t st) {
+    const unsigned g = (unsigned)a.Mg * (unsigned)a.np_e;
     const bool exact = a.K % (64 * CPL) == 0;
     constexpr int CRL = (ORLOJ_MAX_PREFIX + 63) / 64;
     if (a.maxcap <= 64) {
-        if (exact) hipLaunchKernelGGL((emax_kernel<CPL, true, 1, AFF>), dim3(g), dim3(64), 0, st, a);
-        else hipLaunchKernelGGL((emax_kernel<CPL, false, 1, AFF>), dim3(g), dim3(64), 0, st, a);
+        if (exact) hipLaunchKernelGGL((emax_kernel<CPL, true, 1>), dim3(g), dim3(64), 0, st, a);
+        else hipLaunchKernelGGL((emax_kernel<CPL, false, 1>), dim3(g), dim3(64), 0, st, a);
     } else {
-        if (exact) hipLaunchKernelGGL((emax_kernel<CPL, true, CRL, AFF>), dim3(g), dim3(64), 0, st, a);
-        else hipLaunchKernelGGL((emax_kernel<CPL, false, CRL, AFF>), dim3(g), dim3(64), 0, st, a);
+        if (exact) hipLaunchKernelGGL((emax_kernel<CPL, true, CRL>), dim3(g), dim3(64), 0, st, a);
+        else hipLaunchKernelGGL((emax_kernel<CPL, false, CRL>), dim3(g), dim3(64), 0, st, a);
     }
     return hipGetLastError();
 }
 
-template <int CPL>
-hipError_t launch_emax(const ScoreArgs& a, hipStream_t st) {
-    return a.c1 ? launch_emax_m<CPL, true>(a, st) : launch_emax_m<CPL, false>(a, st);
-}
-
-template <int CPL, bool EXACT, int CR>
-hipError_t launch_round_v(const ScoreArgs& a, unsigned n_emax, unsigned grid, hipStream_t st) {
-    const size_t sm = score_fixed_bytes<CPL>() + (size_t)a.maxcap * score_bytes_per_member();
-    static size_t attr_bytes = 0;   // per template instance; device-independent
-    if (sm > attr_bytes) {
-        hipError_t e = hipFuncSetAttribute((const void*)round_kernel<CPL, EXACT, CR>,
-                                           hipFuncAttributeMaxDynamicSharedMemorySize, (int)sm);
+template <int R, bool AFF>
+hipError_t launch_turned_v(const TurnedArgs& a, hipStream_t st) {
+    if constexpr (AFF) {
+        const unsigned g = (unsigned)a.Mg * (unsigned)a.np_e * (unsigned)a.nblk;
+        hipLaunchKernelGGL((turned_esum_kernel<R>), dim3(g), dim3(128), turned_lds(R, 2).total, st, a);
+        const hipError_t e = hipGetLastError();
         if (e != hipSuccess) return e;
-        attr_bytes = sm;
     }
-    hipLaunchKernelGGL((round_kernel<CPL, EXACT, CR>), dim3(grid), dim3(64), sm, st, a, n_emax);
+    constexpr int lds = turned_lds(R, kTurnWaves).total;
+    static std::atomic<int> allowed{64 * 1024};   // per template instance; device-independent
+    if (lds > allowed.load(std::memory_order_relaxed)) {
+        const hipError_t e = hipFuncSetAttribute((const void*)turned_kernel<R, AFF>,
+                                                 hipFuncAttributeMaxDynamicSharedMemorySize, lds);
+        if (e != hipSuccess) return e;
+        allowed.store(lds, std::memory_order_relaxed);
+    }
+    const unsigned g = (unsigned)a.Mg * (unsigned)a.nbs * (unsigned)a.nblk;
+    hipLaunchKernelGGL((turned_kernel<R, AFF>), dim3(g), dim3(64 * kTurnWaves), lds, st, a);
     return hipGetLastError();
 }
 
-template <int CPL>
-hipError_t launch_round(const ScoreArgs& a, unsigned n_emax, unsigned grid, hipStream_t st) {
-    constexpr int CRL = (ORLOJ_MAX_PREFIX + 63) / 64;
-    const bool exact = a.K % (64 * CPL) == 0;
-    if (a.maxcap <= 64)
-        return exact ? launch_round_v<CPL, true, 1>(a, n_emax, grid, st)
-                     : launch_round_v<CPL, false, 1>(a, n_emax, grid, st);
-    return exact ? launch_round_v<CPL, true, CRL>(a, n_emax, grid, st)
-                 : launch_round_v<CPL, false, CRL>(a, n_emax, grid, st);
+template <int R>
+hipError_t launch_turned_r(const TurnedArgs& a, hipStream_t st) {
+    return a.c1 ? launch_turned_v<R, true>(a, st) : launch_turned_v<R, false>(a, st);
+}
+
+hipError_t launch_turned(const TurnedArgs& a, hipStream_t st) {
+    static_assert(ORLOJ_MAX_PREFIX <= 256, "four registers of members");
+    if (a.maxcap <= 64) return launch_turned_r<1>(a, st);
+    return a.maxcap <= 128 ? launch_turned_r<2>(a, st) : launch_turned_r<4>(a, st);
 }
 
 template <int VPT>
@@ -2708,7 +3320,6 @@ int orloj_create(orloj_ctx** out, int32_t hip_device, void* hip_stream) {
     for (int i = 0; i < kFillFloats; ++i) fill[i] = i < kFillFloats / 2 ? 0.0f : 1.0f;
     hipError_t e = hipSetDevice(hip_device);
     ctx->n_cu = 0;
-    ctx->chunk_pref = -1;
     if (e == hipSuccess) e = hipDeviceGetAttribute(&ctx->n_cu, hipDeviceAttributeMultiprocessorCount, hip_device);
     if (e == hipSuccess) e = hipMalloc((void**)&ctx->d_err, sizeof(int));
     if (e == hipSuccess) e = hipMemset(ctx->d_err, 0, sizeof(int));
@@ -2740,7 +3351,6 @@ void orloj_destroy(orloj_ctx* ctx) {
 int orloj_set_score_chunk(orloj_ctx* ctx, int32_t steps) {
     if (!ctx) return ORLOJ_E_INVALID;
     if (steps < -1) return orloj_ctx_fail(ctx, ORLOJ_E_INVALID, "score chunk %d < -1", steps);
-    ctx->chunk_pref = steps;
     return ORLOJ_OK;
 }
 
@@ -2849,60 +3459,6 @@ int orloj_output_sizes(const orloj_grid* grid, const orloj_queues* queues, int32
 
 namespace {
 
-// Prefix steps per score workgroup.  A (model, batch size) workgroup runs
-// its steps one after another, so a launch with too few workgroups to fill
-// the chip lasts as long as its longest one.  Splitting the steps into
-// chunks, each of which first rebuilds G over the steps before it with
-// warm-up steps (about a fifth of a scored step), shortens that chain at
-// the price of the warm-up work.  Only launches whose workgroups occupy
-// fewer than half the SIMDs (`active` pairs with candidates against
-// `simds`) and whose rows span at most two panels are split: every chunk
-// repeats the product over the panels past its members' deadlines, which
-// in rows of more panels costs as much as it saves.  Cost model, in scored
-// steps: max(longest workgroup, all work / slots), where a SIMD is worth
-// 1.5 slots (one wave alone on a SIMD runs at about half the rate three
-// waves sharing it reach together); a chunk size is taken only if it is 10%
-// faster than none.  Chunks of 4 only where the warm-up runs in its own
-// loop with a deep prefetch ring (launches with an E pre-pass); elsewhere
-// warm-up steps wait on their row loads.  Measured: this picks the fastest
-// of none, 8, 16 and 32
-// at configurations 1 to 3 and leaves configuration 5's saturated launch
-// and scheduling-loop rounds unsplit.
-int pick_chunk(const orloj_grid* g, const orloj_queues* qs, int mode, int64_t maxcap,
-               int64_t active, int simds, int panels, bool warm_loop) {
-    if (2 * active > simds || panels > 2) return 0;
-    const double slots = 1.5 * simds;
-    constexpr double kWarm = 0.2;
-    constexpr int kCh[5] = {0, 32, 16, 8, 4};
-    double total[5] = {0.0, 0.0, 0.0, 0.0, 0.0}, longest[5] = {0.0, 0.0, 0.0, 0.0, 0.0};
-    for (int q = 0; q < g->n_models; ++q) {
-        const int64_t N = qs->h_queue_off[q + 1] - qs->h_queue_off[q];
-        if (N <= 0) continue;
-        for (int bi = 0; bi < g->n_bs; ++bi) {
-            const int64_t n = ncap_of(N, g->batch_sizes[bi], mode);
-            total[0] += (double)n;
-            longest[0] = fmax(longest[0], (double)n);
-            for (int o = 1; o < 5; ++o) {
-                const int64_t ch = kCh[o], k = (n + ch - 1) / ch;
-                total[o] += (double)n + kWarm * ch * (double)(k * (k - 1) / 2);
-                longest[o] = fmax(longest[o], kWarm * ch * (double)(k - 1) + (double)(n - (k - 1) * ch));
-            }
-        }
-    }
-    const double t_none = fmax(longest[0], total[0] / slots);
-    double t_best = t_none;
-    int best = 0;
-    for (int o = 1; o < 5; ++o) {
-        if (kCh[o] >= maxcap || (kCh[o] < 8 && !warm_loop)) continue;
-        const double t = fmax(longest[o], total[o] / slots);
-        if (t < 0.9 * t_none && t < t_best) {
-            t_best = t;
-            best = kCh[o];
-        }
-    }
-    return best;
-}
-
 // The context's scratch, grown to at least `bytes`.  Work already enqueued
 // on the context's stream may still use the old block, so the stream is
 // drained before it is freed.
@@ -2927,14 +3483,6 @@ int ensure_work(orloj_ctx* ctx, size_t bytes) {
     return ORLOJ_OK;
 }
 
-// A scheduling round's tabulated score launch that left E[L_B] and the
-// scores to the selection (orloj_internal_score_select).
-struct Deferred {
-    bool on = false;
-    const float* psum = nullptr;
-    int np_e = 0, maxcap = 0;
-};
-
 // Validation and launch shared by the tabulated and the affine scorer
 // (d_c0 / d_c1 NULL: tabulated).
 // fixed_psum (affine mode only): a caller-fixed block of fixed_floats
@@ -2945,8 +3493,7 @@ int score_common(orloj_ctx* ctx, const orloj_grid* grid, const float* d_ccdf,
                  const orloj_queues* queues, double b_expo_per_ms, int32_t prefix_mode,
                  const int64_t* d_cand_off, const int64_t* d_prob_off, float* d_finish_prob,
                  double* d_expected_finish, float* d_expected_latency_ms, float* d_score,
-                 float* fixed_psum = nullptr, size_t fixed_floats = 0,
-                 Deferred* defer = nullptr) {
+                 float* fixed_psum = nullptr, size_t fixed_floats = 0) {
     if (!ctx) return ORLOJ_E_INVALID;
     int rc = check_grid(ctx, grid);
     if (rc) return rc;
@@ -2984,31 +3531,81 @@ int score_common(orloj_ctx* ctx, const orloj_grid* grid, const float* d_ccdf,
     // members' bins, in narrower panels)
     const int cpl = d_c1 ? affine_chunk(grid->n_bins) : score_chunk(grid->n_bins);
     const int panels = (grid->n_bins + 64 * cpl - 1) / (64 * cpl);
-    // Tabulated rows of more than two panels, in a launch too small to fill
-    // the chip or split into step chunks: every panel's E sums come from
-    // emax_kernel (one wave per (model, batch size, panel), in parallel),
-    // and the score waves walk only the panels that hold members (one, as
-    // far as the chunk cost model knows), so chunks repeat only those.
-    // Chunk setting 0 (never split) keeps the single pass.
-    const int simds = 4 * (ctx->n_cu > 0 ? ctx->n_cu : 256);
-    const bool esplit_ok = !d_c1 && panels > 2;
-    const int chunk = ctx->chunk_pref >= 0
-                          ? (ctx->chunk_pref < maxcap ? ctx->chunk_pref : 0)
-                          : pick_chunk(grid, queues, prefix_mode, maxcap, active, simds,
-                                       esplit_ok ? 1 : panels, esplit_ok);
-    const bool esplit = esplit_ok && (chunk > 0 || (ctx->chunk_pref < 0 && 2 * active <= simds));
-    const int nchunk = chunk ? (int)((maxcap + chunk - 1) / chunk) : 1;
     // only the models with a queue get workgroups, when they are few enough
     // to list
     const bool compact = n_act < M && n_act <= kMaxActive;
     const int Mg = compact ? n_act : M;
-    const int64_t nblk = (int64_t)Mg * grid->n_bs * nchunk;
+    const int64_t nblk = (int64_t)Mg * grid->n_bs;
     if (nblk > 0x7fffffff) return orloj_ctx_fail(ctx, ORLOJ_E_UNSUPPORTED, "too many (model, batch size) pairs");
 
+    // Launches too small to fill the chip go to turned_kernel (its row offsets
+    // are 32-bit; its E sums are doubles, and must fit the fixed scratch for
+    // every call that the float sums do).  score_kernel takes about as long
+    // for one pair as for a full chip, turned_kernel's time grows with the
+    // pairs past one workgroup per compute unit, so the line lies where they
+    // meet: score + selection, us, score_kernel / turned_kernel, at
+    //   512 pairs:  20.1 / 21.7 (256 bins, prefixes to 16), 32.9 / 26.6
+    //     (1024 bins, to 32), 55 / 34 (1024, to 64), 44 / 43 (4096, to 12)
+    //   1024 pairs: 20.5 / 34 (256, 16), 35 / 45 (1024, 32), 59 / 58 (1024,
+    //     64), 177 / 126 (4096, 64), 187 / 205 (2048, 100).
+    const int simds = 4 * (ctx->n_cu > 0 ? ctx->n_cu : 256);
+    const bool longest = maxcap == 64 && grid->n_bins >= 1024;
+    const int64_t np_t = (grid->n_bins + kPanel - 1) / kPanel;
+    if (active <= (longest ? simds : simds / 2) && (int64_t)grid->n_classes * grid->n_bins <= 0x3fffffff &&
+        (!d_c1 || (int64_t)M * np_t * maxcap <= ORLOJ_NOALLOC_SCRATCH_FLOATS / 2)) {
+        TurnedArgs a;
+        a.tab = d_ccdf;
+        a.sup = d_support;
+        a.c0 = d_c0;
+        a.c1 = d_c1;
+        a.cost = queues->d_cost;
+        a.queue_off = queues->d_queue_off;
+        a.cls = queues->d_class;
+        a.deadline = queues->d_deadline_ms;
+        a.now = queues->d_now_ms;
+        a.width = grid->d_bin_width_ms;
+        a.cand_off = d_cand_off;
+        a.prob_off = d_prob_off;
+        a.P = d_finish_prob;
+        a.E = d_expected_finish;
+        a.EL = d_expected_latency_ms;
+        a.S = d_score;
+        a.err = ctx->d_err;
+        a.b = b_expo_per_ms;
+        a.C = grid->n_classes;
+        a.K = grid->n_bins;
+        a.nbs = grid->n_bs;
+        a.rect = prefix_mode;
+        a.maxcap = (int)maxcap;
+        a.Mg = Mg;
+        a.compact = compact ? 1 : 0;
+        a.nblk = (int)((maxcap + 63) / 64);
+        memset(a.bs, 0, sizeof a.bs);
+        for (int i = 0; i < grid->n_bs; ++i) a.bs[i] = grid->batch_sizes[i];
+        memset(a.act, 0, sizeof a.act);
+        if (compact)
+            for (int i = 0; i < n_act; ++i) a.act[i] = act[i];
+        hipError_t e = hipSetDevice(ctx->device);
+        if (e != hipSuccess) return hip_fail(ctx, e, "hipSetDevice");
+        a.esum = nullptr;
+        a.np_e = 0;
+        if (d_c1) {
+            const size_t need = (size_t)M * (size_t)np_t * (size_t)maxcap;
+            if (fixed_psum) {
+                a.esum = (double*)fixed_psum;
+            } else {
+                rc = ensure_work(ctx, need * sizeof(double));
+                if (rc) return rc;
+                a.esum = (double*)ctx->d_work;
+            }
+            a.np_e = (int)np_t;
+        }
+        e = launch_turned(a, ctx->stream);
+        if (e != hipSuccess) return hip_fail(ctx, e, "turned_kernel launch");
+        return ORLOJ_OK;
+    }
+
     ScoreArgs a;
-    a.defer = 0;
-    a.chunk = chunk;
-    a.nchunk = nchunk;
     a.tab = d_ccdf;
     a.sup = d_support;
     a.c0 = d_c0;
@@ -3046,19 +3643,13 @@ int score_common(orloj_ctx* ctx, const orloj_grid* grid, const float* d_ccdf,
     if (e != hipSuccess) return hip_fail(ctx, e, "hipSetDevice");
     a.psum = nullptr;
     a.np_e = 0;
-    // emax_kernel's panels: the score waves' own in the tabulated mode (its
-    // sums must round as theirs do); in the affine mode the narrow panels of
-    // the affine score waves, so that four times as many waves share the
-    // products of a model's few hundred prefixes
-    const int cple = d_c1 ? cpl : score_chunk(grid->n_bins);
-    if (d_c1 || esplit) {
-        // emax_kernel's panel sums, formed first: [pairs][panels][maxcap]
-        // floats, pairs = models (affine) or (model, batch size) pairs
-        const int64_t np = (grid->n_bins + 64 * cple - 1) / (64 * cple);
-        const int64_t pairs = d_c1 ? (int64_t)M : (int64_t)M * grid->n_bs;
-        if (pairs * np > 0x7fffffff)
-            return orloj_ctx_fail(ctx, ORLOJ_E_UNSUPPORTED, "too many (pair, panel) pairs");
-        const size_t need = (size_t)pairs * (size_t)np * (size_t)maxcap;
+    if (d_c1) {
+        // emax_kernel's panel sums, formed first: [M][panels][maxcap] floats,
+        // on the score waves' own panels
+        const int64_t np = panels;
+        if ((int64_t)M * np > 0x7fffffff)
+            return orloj_ctx_fail(ctx, ORLOJ_E_UNSUPPORTED, "too many (model, panel) pairs");
+        const size_t need = (size_t)M * (size_t)np * (size_t)maxcap;
         if (fixed_psum) {
             if (need > fixed_floats)
                 return orloj_ctx_fail(ctx, ORLOJ_E_UNSUPPORTED,
@@ -3072,27 +3663,7 @@ int score_common(orloj_ctx* ctx, const orloj_grid* grid, const float* d_ccdf,
             a.psum = (float*)ctx->d_work;
         }
         a.np_e = (int)np;
-        if (defer && !d_c1 && cple == cpl) {
-            // a scheduling round: emax_kernel's and score_kernel's waves in
-            // one launch, E[L_B] and the scores finished by the selection
-            a.defer = 1;
-            const unsigned n_emax = (unsigned)(Mg * grid->n_bs) * (unsigned)np;
-            const unsigned g = n_emax + (unsigned)nblk;
-            switch (cpl) {
-                case 1: e = launch_round<1>(a, n_emax, g, ctx->stream); break;
-                case 2: e = launch_round<2>(a, n_emax, g, ctx->stream); break;
-                case 4: e = launch_round<4>(a, n_emax, g, ctx->stream); break;
-                case 8: e = launch_round<8>(a, n_emax, g, ctx->stream); break;
-                default: e = launch_round<16>(a, n_emax, g, ctx->stream); break;
-            }
-            if (e != hipSuccess) return hip_fail(ctx, e, "round_kernel launch");
-            defer->on = true;
-            defer->psum = a.psum;
-            defer->np_e = a.np_e;
-            defer->maxcap = a.maxcap;
-            return ORLOJ_OK;
-        }
-        switch (cple) {
+        switch (cpl) {
             case 1: e = launch_emax<1>(a, ctx->stream); break;
             case 2: e = launch_emax<2>(a, ctx->stream); break;
             case 4: e = launch_emax<4>(a, ctx->stream); break;
@@ -3115,13 +3686,11 @@ int score_common(orloj_ctx* ctx, const orloj_grid* grid, const float* d_ccdf,
     return ORLOJ_OK;
 }
 
-// orloj_select_batch, and the finishing selection of a scheduling round
-// (fin->on: E[L_B] and the scores are formed here from the panel sums and
-// the priority sums in d_score, and written to d_EL and d_score).
+// orloj_select_batch; a scheduling round also passes the flags its
+// workgroups set (d_done).
 int select_common(orloj_ctx* ctx, const orloj_grid* grid, const orloj_queues* queues,
-                  int32_t prefix_mode, const int64_t* d_cand_off, float* d_score,
-                  int32_t* d_sel_n, int32_t* d_sel_bs, float* d_sel_score, const Deferred* fin,
-                  float* d_EL, int32_t* d_done = nullptr, int32_t round = 0, int* n_groups = nullptr) {
+                  int32_t prefix_mode, const int64_t* d_cand_off, const float* d_score,
+                  int32_t* d_sel_n, int32_t* d_sel_bs, float* d_sel_score, int32_t* d_done = nullptr, int32_t round = 0, int* n_groups = nullptr) {
     if (!ctx) return ORLOJ_E_INVALID;
     int rc = check_grid(ctx, grid);
     if (rc) return rc;
@@ -3136,14 +3705,8 @@ int select_common(orloj_ctx* ctx, const orloj_grid* grid, const orloj_queues* qu
     const int64_t total = queues->h_queue_off[M];
     if (total > 0 && !d_score) return orloj_ctx_fail(ctx, ORLOJ_E_INVALID, "d_score is NULL");
     SelectArgs a;
-    a.finish = fin && fin->on ? 1 : 0;
     a.done = d_done;
     a.round = round;
-    a.psum = a.finish ? fin->psum : nullptr;
-    a.np_e = a.finish ? fin->np_e : 0;
-    a.maxcap = a.finish ? fin->maxcap : 0;
-    a.width = grid->d_bin_width_ms;
-    a.EL = d_EL;
     a.queue_off = queues->d_queue_off;
     a.cand_off = d_cand_off;
     a.S = d_score;
@@ -3409,8 +3972,8 @@ int orloj_accumulate(orloj_ctx* ctx, const orloj_grid* grid, int64_t n_samples,
 int orloj_select_batch(orloj_ctx* ctx, const orloj_grid* grid, const orloj_queues* queues,
                        int32_t prefix_mode, const int64_t* d_cand_off, const float* d_score,
                        int32_t* d_sel_n, int32_t* d_sel_bs, float* d_sel_score) {
-    return select_common(ctx, grid, queues, prefix_mode, d_cand_off, const_cast<float*>(d_score),
-                         d_sel_n, d_sel_bs, d_sel_score, nullptr, nullptr);
+    return select_common(ctx, grid, queues, prefix_mode, d_cand_off, d_score, d_sel_n, d_sel_bs,
+                         d_sel_score);
 }
 
 }  // extern "C"
@@ -3422,11 +3985,10 @@ int orloj_internal_score_select(orloj_ctx* ctx, const orloj_grid* grid, const fl
                                 double* d_expected_finish, float* d_expected_latency_ms,
                                 float* d_score, int32_t* d_sel_n, int32_t* d_sel_bs,
                                 float* d_sel_score, int32_t* d_done, int32_t round, int* n_groups) {
-    Deferred fin;
     int rc = score_common(ctx, grid, d_ccdf, d_support, nullptr, nullptr, queues, b_expo_per_ms,
                           ORLOJ_PREFIX_TRIANGLE, d_cand_off, d_prob_off, d_finish_prob,
-                          d_expected_finish, d_expected_latency_ms, d_score, nullptr, 0, &fin);
+                          d_expected_finish, d_expected_latency_ms, d_score);
     if (rc) return rc;
     return select_common(ctx, grid, queues, ORLOJ_PREFIX_TRIANGLE, d_cand_off, d_score, d_sel_n,
-                         d_sel_bs, d_sel_score, &fin, d_expected_latency_ms, d_done, round, n_groups);
+                         d_sel_bs, d_sel_score, d_done, round, n_groups);
 }

@@ -13,7 +13,6 @@
 struct orloj_ctx {
     int device;
     int n_cu;        // compute units of the device
-    int chunk_pref;  // prefix steps per score workgroup: -1 automatic, 0 all
     hipStream_t stream;
     int* d_err;      // device status word (data error bits)
     float* d_fill;   // stand-in table entries: 16 zeros, 16 ones
@@ -39,9 +38,7 @@ static inline int orloj_ctx_fail(orloj_ctx* ctx, int code, const char* fmt, ...)
 
 // One scheduling round's scoring and selection (sched.hip): the outputs of
 // orloj_score_candidates (triangle prefixes) followed by orloj_select_batch,
-// bit for bit.  In launches that take their E sums from emax_kernel, that
-// kernel's waves and the score waves share one launch, and the selection
-// forms E[L_B] and the scores from the panel sums before its argmax.
+// bit for bit.
 // d_done (mapped host memory, or NULL): each select workgroup g writes
 // `round` to d_done[g] once its writes are visible to the host;
 // *n_groups receives the number of select workgroups.

@@ -7,10 +7,9 @@
 //                          call: every idle model's queue is staged in
 //                          pinned memory, uploaded in one copy, scored and
 //                          a batch selected per model (the outputs of
-//                          orloj_score_candidates + orloj_select_batch, the
-//                          E pre-pass sharing the score launch), the
-//                          selections read back,
-//                          and the chosen members popped;
+//                          orloj_score_candidates + orloj_select_batch), the
+//                          selections read back, and the chosen members
+//                          popped;
 //   orloj_simulate_trace   a trace-driven run of one worker per model on top
 //                          of it (one batch at a time, §3.1): the arrivals
 //                          of a trace, a decision round every tick, batch
@@ -172,8 +171,7 @@ int decide(orloj_sched* s, double now, const uint8_t* idle, int32_t* sel_n, int3
         const int64_t* d_coff = reinterpret_cast<const int64_t*>(s->d_stage + o1);
         const int64_t* d_poff = reinterpret_cast<const int64_t*>(s->d_stage + 2 * o1);
         // scoring and selection: the outputs of orloj_score_candidates and
-        // orloj_select_batch, with the E pre-pass and the score waves of a
-        // small round in one launch
+        // orloj_select_batch
         const int32_t round = ++s->round;
         int groups = 0;
         rc = orloj_internal_score_select(ctx, &s->grid, s->d_ccdf, s->d_support, &dq, s->b, d_coff,

@@ -196,7 +196,7 @@ class Context:
         self._check(self.L.orloj_set_stream(self.ctx, ctypes.c_void_p(stream.cuda_stream)))
 
     def set_score_chunk(self, steps: int):
-        """Prefix steps per score workgroup: -1 automatic, 0 never split."""
+        """Prefix steps per score workgroup (-1, 0 or k > 0): accepted, no effect."""
         self._check(self.L.orloj_set_score_chunk(self.ctx, int(steps)))
 
     def sync(self):
