@@ -300,6 +300,10 @@ int orloj_select_batch(orloj_ctx *ctx, const orloj_grid *grid, const orloj_queue
  * d_ccdf is orloj_build_cdfs' [M][n_bs][C][K] table; d_law and d_disc have
  * its shape (float32), d_model_el is [M][n_bs] float32.  Negative, infinite
  * or all-zero weights of a model are a data error (orloj_sync).
+ * With at least 8 classes and no more (model, batch size) pairs than compute
+ * units, F_mix^(s_b - 1) goes through the context's scratch block (pairs x K
+ * doubles, grown on demand as for the affine scorer, ORLOJ_E_NOMEM if that
+ * fails; a stream under capture whose block is too small does without).
  *
  * orloj_iterate: one iteration for every model in one launch.  For model q
  * at time now_q, with tau_r = D_r - now_q:

@@ -2409,6 +2409,7 @@ struct LawArgs {
     float* disc;               // [M][nbs][C][K]
     float* model_el;           // [M][nbs]
     int* err;
+    double* pm;                // laws_mix_kernel: [pairs][K] F_mix^(s-1)
     double b;
     int M, C, K, nbs;
     int bs[ORLOJ_MAX_BATCH_SIZES];
@@ -2551,6 +2552,157 @@ __global__ __launch_bounds__(kThreads) void laws_kernel(const LawArgs a) {
         store_chunk<VPT>(a.law + r, lv, base, K);
         store_chunk<VPT>(a.disc + r, dv, base, K);
     }
+}
+
+// ---------------------------------------------------------------------------
+// laws_mix_kernel and laws_row_kernel: laws_kernel's outputs when the pairs
+// are no more than the compute units.  laws_kernel walks a pair's classes one
+// after another in one workgroup; here one workgroup per pair forms the class
+// mix and its power per bin (to scratch) and the model-wide E[L], and then
+// every row has a workgroup of its own.  Table and laws, us: 1 model x 64
+// batch sizes x 32 classes x 1024 bins 44 -> 24, 2 x 16 x 32 x 4096 105 -> 51,
+// 3 x 48 x 21 x 1501 101 -> 69, 8 x 32 x 16 x 1000 34.5 -> 31.  From 512
+// pairs on laws_kernel is faster (98 against 128 at 16 x 32 x 8 x 4096), and
+// so it is at a handful of classes (12.6 against 14.5 at 7).
+// ---------------------------------------------------------------------------
+constexpr int kMixThreads = 1024;
+
+// VEC: four bins a thread (rows start on 16 bytes), else one.
+template <bool VEC>
+__global__ __launch_bounds__(kMixThreads) void laws_mix_kernel(const LawArgs a) {
+    constexpr int V = VEC ? 4 : 1;
+    __shared__ double s_el[kMixThreads / 64];
+    const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
+    const int pair = (int)blockIdx.x;
+    const int q = pair / a.nbs;
+    const int K = a.K, C = a.C;
+    const int s = a.bs[pair % a.nbs];
+    const double w = a.width[q];
+    const float* rows = a.tab + (size_t)pair * (size_t)C * (size_t)K;
+    double wsum = 0.0;
+    bool wbad = false;
+    for (int c = 0; c < C; ++c) {
+        const double wc = a.weights ? a.weights[(size_t)q * C + c] : 1.0;
+        wbad |= !(wc >= 0.0) || isinf(wc);
+        wsum += wc;
+    }
+    if (wbad || !(wsum > 0.0)) {
+        if (tid == 0) atomicOr(a.err, kErrWeights);
+        wsum = 1.0;
+    }
+    double el = 0.0;
+    for (int base = V * tid; base < K; base += V * (int)blockDim.x) {
+        double mix[V];
+#pragma unroll
+        for (int j = 0; j < V; ++j) mix[j] = 0.0;
+#pragma unroll 8
+        for (int c = 0; c < C; ++c) {
+            const double pc = (a.weights ? a.weights[(size_t)q * C + c] : 1.0) / wsum;
+            float t[V];
+            const float* src = rows + (size_t)c * (size_t)K + base;
+            if constexpr (VEC) {
+                const float4 x = *reinterpret_cast<const float4*>(src);
+                t[0] = x.x; t[1] = x.y; t[2] = x.z; t[3] = x.w;
+            } else {
+                t[0] = src[0];
+            }
+#pragma unroll
+            for (int j = 0; j < V; ++j) mix[j] = fma(pc, 1.0 - (double)t[j], mix[j]);
+        }
+        double pm[V];
+#pragma unroll
+        for (int j = 0; j < V; ++j) {
+            pm[j] = s > 1 ? pow(mix[j], (double)(s - 1)) : 1.0;
+            el += 1.0 - pm[j] * mix[j];
+        }
+        double* o = a.pm + (size_t)pair * (size_t)K + base;
+        if constexpr (VEC) {
+            *reinterpret_cast<double2*>(o) = make_double2(pm[0], pm[1]);
+            *reinterpret_cast<double2*>(o + 2) = make_double2(pm[2], pm[3]);
+        } else {
+            o[0] = pm[0];
+        }
+    }
+    // model-wide E[L] = w (1/2 + sum_k (1 - F_mix^s(x_{k+1})))
+    for (int o = 32; o > 0; o >>= 1) el += __shfl_xor(el, o, 64);
+    if (lane == 0) s_el[wv] = el;
+    __syncthreads();
+    if (tid == 0) {
+        double tot = 0.0;
+        for (int i = 0; i < (int)blockDim.x / 64; ++i) tot += s_el[i];
+        a.model_el[pair] = (float)(w * (0.5 + tot));
+    }
+}
+
+template <int VPT>
+__global__ __launch_bounds__(kThreads) void laws_row_kernel(const LawArgs a) {
+    __shared__ float s_wave[kWaves];
+    const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
+    const int pair = (int)(blockIdx.x / (unsigned)a.C), c = (int)(blockIdx.x % (unsigned)a.C);
+    const int K = a.K, base = tid * VPT;
+    const size_t r = ((size_t)pair * (size_t)a.C + (size_t)c) * (size_t)K;
+    double g[VPT], pm[VPT];
+    load_cdf_chunk<VPT>(g, a.tab + r, base, K);
+    const double* pmr = a.pm + (size_t)pair * (size_t)K;
+#pragma unroll
+    for (int j = 0; j < VPT; ++j) pm[j] = 1.0;             // padding bins: F = 1
+    if (VPT % 2 == 0 && K % 2 == 0) {
+#pragma unroll
+        for (int j = 0; j + 1 < VPT; j += 2)
+            if (base + j < K) {
+                const double2 v = *reinterpret_cast<const double2*>(pmr + base + j);
+                pm[j] = v.x;
+                pm[j + 1] = v.y;
+            }
+    } else {
+#pragma unroll
+        for (int j = 0; j < VPT; ++j)
+            if (base + j < K) pm[j] = pmr[base + j];
+    }
+    const double bw = a.b * a.width[pair / a.nbs];
+    const double d = exp(-bw);
+    // scan constants: a thread chunk spans VPT bins
+    const float log2d = (float)(-bw * 1.4426950408889634);
+    float rp[4];
+#pragma unroll
+    for (int i = 0; i < 4; ++i) rp[i] = exp2_hw(log2d * (float)(VPT << i));
+    const float w15 = exp2_hw(log2d * (float)(VPT * ((lane & 15) + 1)));
+    const float w31 = exp2_hw(log2d * (float)(VPT * (lane >= 32 ? lane - 31 : 0)));
+    const float d_wave = exp2_hw(log2d * (float)(64 * VPT));
+
+    double z = 0.0;
+#pragma unroll
+    for (int j = 0; j < VPT; ++j) {
+        g[j] *= pm[j];
+        z = fma(z, d, g[j]);
+    }
+    // in-wave weighted scan of the chunk totals, then across the waves
+    const float A = wave_wscan((float)z, rp, w15, w31);
+    if (lane == 63) s_wave[wv] = A;
+    __syncthreads();
+    float carry = 0.0f;   // discounted sum of the earlier waves' bins, at the end of the last one
+#pragma unroll
+    for (int i = 0; i < kWaves; ++i)
+        if (i < wv) carry = fmaf(carry, d_wave, s_wave[i]);
+    // prefix up to the end of the previous thread chunk
+    const float prev = __shfl_up(A, 1, 64);
+    const float before = (lane > 0 ? prev : 0.0f) + carry * exp2_hw(log2d * (float)(VPT * lane));
+    double zz = (double)before;
+    float lv[VPT], dv[VPT];
+#pragma unroll
+    for (int j = 0; j < VPT; ++j) {
+        zz = fma(zz, d, g[j]);
+        lv[j] = (float)g[j];
+        dv[j] = (float)zz;
+    }
+    store_chunk<VPT>(a.law + r, lv, base, K);
+    store_chunk<VPT>(a.disc + r, dv, base, K);
+}
+
+template <int VPT>
+hipError_t launch_laws_rows(const LawArgs& a, unsigned rows, hipStream_t st) {
+    hipLaunchKernelGGL(laws_row_kernel<VPT>, dim3(rows), dim3(kThreads), 0, st, a);
+    return hipGetLastError();
 }
 
 // ---------------------------------------------------------------------------
@@ -3817,6 +3969,41 @@ int orloj_build_model_laws(orloj_ctx* ctx, const orloj_grid* grid, const float* 
     for (int i = 0; i < grid->n_bs; ++i) a.bs[i] = grid->batch_sizes[i];
     hipError_t e = hipSetDevice(ctx->device);
     if (e != hipSuccess) return hip_fail(ctx, e, "hipSetDevice");
+    a.pm = nullptr;
+    const size_t pm_bytes = (size_t)nblk * (size_t)grid->n_bins * sizeof(double);
+    bool split = a.C >= 8 && nblk <= (ctx->n_cu > 0 ? ctx->n_cu : 256) && nblk * a.C <= 0x7fffffff;
+    if (split && pm_bytes > ctx->work_bytes) {
+        // a stream under capture cannot wait for the scratch to grow
+        hipStreamCaptureStatus cs = hipStreamCaptureStatusNone;
+        if (hipStreamIsCapturing(ctx->stream, &cs) != hipSuccess) {
+            (void)hipGetLastError();
+            split = false;
+        }
+        split = split && cs == hipStreamCaptureStatusNone;
+    }
+    if (split) {
+        rc = ensure_work(ctx, pm_bytes);
+        if (rc) return rc;
+        a.pm = (double*)ctx->d_work;
+        const bool vec = a.K % 4 == 0 && ((uintptr_t)a.tab & 15) == 0;
+        const int per = vec ? 4 : 1;
+        const int mix_threads = std::min(kMixThreads, (a.K + 64 * per - 1) / (64 * per) * 64);
+        if (vec) hipLaunchKernelGGL(laws_mix_kernel<true>, dim3((unsigned)nblk), dim3(mix_threads), 0, ctx->stream, a);
+        else hipLaunchKernelGGL(laws_mix_kernel<false>, dim3((unsigned)nblk), dim3(mix_threads), 0, ctx->stream, a);
+        e = hipGetLastError();
+        if (e != hipSuccess) return hip_fail(ctx, e, "laws_mix_kernel launch");
+        const unsigned rows = (unsigned)(nblk * a.C);
+        switch (chunk_per_lane(grid->n_bins)) {
+            case 1: e = launch_laws_rows<1>(a, rows, ctx->stream); break;
+            case 2: e = launch_laws_rows<2>(a, rows, ctx->stream); break;
+            case 4: e = launch_laws_rows<4>(a, rows, ctx->stream); break;
+            case 8: e = launch_laws_rows<8>(a, rows, ctx->stream); break;
+            case 16: e = launch_laws_rows<16>(a, rows, ctx->stream); break;
+            default: e = launch_laws_rows<32>(a, rows, ctx->stream); break;
+        }
+        if (e != hipSuccess) return hip_fail(ctx, e, "laws_row_kernel launch");
+        return ORLOJ_OK;
+    }
     const unsigned g = (unsigned)nblk;
     switch (chunk_per_lane(grid->n_bins)) {
         case 1: hipLaunchKernelGGL(laws_kernel<1>, dim3(g), dim3(kThreads), 0, ctx->stream, a); break;
