@@ -224,7 +224,9 @@ int orloj_score_candidates(orloj_ctx *ctx, const orloj_grid *grid, const float *
  * The sums of 1 - G behind E[X] do not depend on the batch size, so they
  * are formed once per (model, prefix length) into a scratch block the
  * context owns (M x ceil(K / 256) x the longest prefix floats, doubles where
- * that is at most 2^19 sums and the launch is small).  The
+ * that is at most 2^19 sums and the launch is small; the doubles have a block
+ * of their own, and a call that cannot have it, for want of memory or because
+ * its stream is under capture, uses the floats).  The
  * first call that needs a larger block waits for the context's
  * stream, frees the old block and allocates the new one (ORLOJ_E_NOMEM if
  * that fails); the block is reused by later calls and freed by
@@ -301,9 +303,9 @@ int orloj_select_batch(orloj_ctx *ctx, const orloj_grid *grid, const orloj_queue
  * its shape (float32), d_model_el is [M][n_bs] float32.  Negative, infinite
  * or all-zero weights of a model are a data error (orloj_sync).
  * With at least 8 classes and no more (model, batch size) pairs than compute
- * units, F_mix^(s_b - 1) goes through the context's scratch block (pairs x K
- * doubles, grown on demand as for the affine scorer, ORLOJ_E_NOMEM if that
- * fails; a stream under capture whose block is too small does without).
+ * units, F_mix^(s_b - 1) goes through a scratch block of the context (pairs x
+ * K doubles, grown on demand; without memory for it, and on a stream under
+ * capture, the laws are formed without it: the laws and prefixes have the same bits).
  *
  * orloj_iterate: one iteration for every model in one launch.  For model q
  * at time now_q, with tau_r = D_r - now_q:

@@ -3458,8 +3458,7 @@ int orloj_create(orloj_ctx** out, int32_t hip_device, void* hip_stream) {
     ctx->stream = (hipStream_t)hip_stream;
     ctx->d_err = nullptr;
     ctx->d_fill = nullptr;
-    ctx->d_work = nullptr;
-    ctx->work_bytes = 0;
+    ctx->work = ctx->esum = ctx->mix = orloj_block{nullptr, 0};
     ctx->noalloc_scratch = nullptr;
     ctx->noalloc_err = hipSuccess;
     ctx->msg[0] = 0;
@@ -3496,7 +3495,8 @@ void orloj_destroy(orloj_ctx* ctx) {
     (void)hipStreamSynchronize(ctx->stream);
     if (ctx->d_err) (void)hipFree(ctx->d_err);
     if (ctx->d_fill) (void)hipFree(ctx->d_fill);
-    if (ctx->d_work) (void)hipFree(ctx->d_work);
+    for (const orloj_block& b : {ctx->work, ctx->esum, ctx->mix})
+        if (b.p) (void)hipFree(b.p);
     delete ctx;
 }
 
@@ -3508,7 +3508,7 @@ int orloj_set_score_chunk(orloj_ctx* ctx, int32_t steps) {
 
 int orloj_set_stream(orloj_ctx* ctx, void* hip_stream) {
     if (!ctx) return ORLOJ_E_INVALID;
-    if ((hipStream_t)hip_stream != ctx->stream && ctx->d_work) {
+    if ((hipStream_t)hip_stream != ctx->stream && (ctx->work.p || ctx->esum.p || ctx->mix.p)) {
         // calls still queued on the old stream may use the scratch
         hipError_t e = hipSetDevice(ctx->device);
         if (e == hipSuccess) e = hipStreamSynchronize(ctx->stream);
@@ -3611,28 +3611,38 @@ int orloj_output_sizes(const orloj_grid* grid, const orloj_queues* queues, int32
 
 namespace {
 
-// The context's scratch, grown to at least `bytes`.  Work already enqueued
-// on the context's stream may still use the old block, so the stream is
-// drained before it is freed.
-int ensure_work(orloj_ctx* ctx, size_t bytes) {
-    if (bytes <= ctx->work_bytes) return ORLOJ_OK;
+// A scratch block of the context, grown to at least `bytes`.  Work already
+// enqueued on the context's stream may still use the old block, so the stream
+// is drained before it is freed.
+int ensure_block(orloj_ctx* ctx, orloj_block* blk, size_t bytes) {
+    if (bytes <= blk->bytes) return ORLOJ_OK;
     hipError_t e = hipStreamSynchronize(ctx->stream);
     if (e != hipSuccess) return hip_fail(ctx, e, "hipStreamSynchronize");
-    if (ctx->d_work) {
-        e = hipFree(ctx->d_work);
-        ctx->d_work = nullptr;
-        ctx->work_bytes = 0;
+    if (blk->p) {
+        e = hipFree(blk->p);
+        blk->p = nullptr;
+        blk->bytes = 0;
         if (e != hipSuccess) return hip_fail(ctx, e, "hipFree");
     }
-    e = hipMalloc(&ctx->d_work, bytes);
+    e = hipMalloc(&blk->p, bytes);
     if (e != hipSuccess) {
-        ctx->d_work = nullptr;
-        return e == hipErrorOutOfMemory
-                   ? orloj_ctx_fail(ctx, ORLOJ_E_NOMEM, "scratch of %zu bytes", bytes)
-                   : hip_fail(ctx, e, "hipMalloc");
+        blk->p = nullptr;
+        if (e != hipErrorOutOfMemory) return hip_fail(ctx, e, "hipMalloc");
+        (void)hipGetLastError();
+        return orloj_ctx_fail(ctx, ORLOJ_E_NOMEM, "scratch of %zu bytes", bytes);
     }
-    ctx->work_bytes = bytes;
+    blk->bytes = bytes;
     return ORLOJ_OK;
+}
+
+// Whether the context's stream is being captured (or cannot say).
+bool capturing(orloj_ctx* ctx) {
+    hipStreamCaptureStatus cs = hipStreamCaptureStatusNone;
+    if (hipStreamIsCapturing(ctx->stream, &cs) != hipSuccess) {
+        (void)hipGetLastError();
+        return true;
+    }
+    return cs != hipStreamCaptureStatusNone;
 }
 
 // Validation and launch shared by the tabulated and the affine scorer
@@ -3703,8 +3713,24 @@ int score_common(orloj_ctx* ctx, const orloj_grid* grid, const float* d_ccdf,
     const int simds = 4 * (ctx->n_cu > 0 ? ctx->n_cu : 256);
     const bool longest = maxcap == 64 && grid->n_bins >= 1024;
     const int64_t np_t = (grid->n_bins + kPanel - 1) / kPanel;
-    if (active <= (longest ? simds : simds / 2) && (int64_t)grid->n_classes * grid->n_bins <= 0x3fffffff &&
-        (!d_c1 || (int64_t)M * np_t * maxcap <= ORLOJ_NOALLOC_SCRATCH_FLOATS / 2)) {
+    bool turned = active <= (longest ? simds : simds / 2) &&
+                  (int64_t)grid->n_classes * grid->n_bins <= 0x3fffffff &&
+                  (!d_c1 || (int64_t)M * np_t * maxcap <= ORLOJ_NOALLOC_SCRATCH_FLOATS / 2);
+    if (turned && d_c1 && !fixed_psum) {
+        // where the doubles cannot be had (a stream under capture whose block
+        // is too small, no memory left), score_kernel's float sums may be there
+        const size_t need = (size_t)M * (size_t)np_t * (size_t)maxcap * sizeof(double);
+        if (need > ctx->esum.bytes && capturing(ctx)) {
+            turned = false;
+        } else {
+            hipError_t e = hipSetDevice(ctx->device);
+            if (e != hipSuccess) return hip_fail(ctx, e, "hipSetDevice");
+            rc = ensure_block(ctx, &ctx->esum, need);
+            if (rc && rc != ORLOJ_E_NOMEM) return rc;
+            turned = rc == ORLOJ_OK;
+        }
+    }
+    if (turned) {
         TurnedArgs a;
         a.tab = d_ccdf;
         a.sup = d_support;
@@ -3742,14 +3768,7 @@ int score_common(orloj_ctx* ctx, const orloj_grid* grid, const float* d_ccdf,
         a.esum = nullptr;
         a.np_e = 0;
         if (d_c1) {
-            const size_t need = (size_t)M * (size_t)np_t * (size_t)maxcap;
-            if (fixed_psum) {
-                a.esum = (double*)fixed_psum;
-            } else {
-                rc = ensure_work(ctx, need * sizeof(double));
-                if (rc) return rc;
-                a.esum = (double*)ctx->d_work;
-            }
+            a.esum = (double*)(fixed_psum ? (void*)fixed_psum : ctx->esum.p);
             a.np_e = (int)np_t;
         }
         e = launch_turned(a, ctx->stream);
@@ -3810,9 +3829,9 @@ int score_common(orloj_ctx* ctx, const orloj_grid* grid, const float* d_ccdf,
                                       need, fixed_floats);
             a.psum = fixed_psum;
         } else {
-            rc = ensure_work(ctx, need * sizeof(float));
+            rc = ensure_block(ctx, &ctx->work, need * sizeof(float));
             if (rc) return rc;
-            a.psum = (float*)ctx->d_work;
+            a.psum = (float*)ctx->work.p;
         }
         a.np_e = (int)np;
         switch (cpl) {
@@ -3972,19 +3991,16 @@ int orloj_build_model_laws(orloj_ctx* ctx, const orloj_grid* grid, const float* 
     a.pm = nullptr;
     const size_t pm_bytes = (size_t)nblk * (size_t)grid->n_bins * sizeof(double);
     bool split = a.C >= 8 && nblk <= (ctx->n_cu > 0 ? ctx->n_cu : 256) && nblk * a.C <= 0x7fffffff;
-    if (split && pm_bytes > ctx->work_bytes) {
-        // a stream under capture cannot wait for the scratch to grow
-        hipStreamCaptureStatus cs = hipStreamCaptureStatusNone;
-        if (hipStreamIsCapturing(ctx->stream, &cs) != hipSuccess) {
-            (void)hipGetLastError();
-            split = false;
-        }
-        split = split && cs == hipStreamCaptureStatusNone;
+    // no scratch in a captured launch, which a later, larger call would free
+    if (split && !capturing(ctx)) {
+        rc = ensure_block(ctx, &ctx->mix, pm_bytes);
+        if (rc && rc != ORLOJ_E_NOMEM) return rc;
+        split = rc == ORLOJ_OK;  // no memory left: laws_kernel does without
+    } else {
+        split = false;
     }
     if (split) {
-        rc = ensure_work(ctx, pm_bytes);
-        if (rc) return rc;
-        a.pm = (double*)ctx->d_work;
+        a.pm = (double*)ctx->mix.p;
         const bool vec = a.K % 4 == 0 && ((uintptr_t)a.tab & 15) == 0;
         const int per = vec ? 4 : 1;
         const int mix_threads = std::min(kMixThreads, (a.K + 64 * per - 1) / (64 * per) * 64);
@@ -4094,9 +4110,9 @@ int orloj_iterate(orloj_ctx* ctx, const orloj_grid* grid, const int32_t* d_suppo
     if (longest > kIterWideQueue && 4 * (int64_t)M <= n_cu) {
         const int P = (int)((longest + kDropPart - 1) / kDropPart);
         const size_t n = (size_t)M * (size_t)P * (size_t)a.nbs;
-        int rc2 = ensure_work(ctx, 2 * n * sizeof(int32_t));
+        int rc2 = ensure_block(ctx, &ctx->work, 2 * n * sizeof(int32_t));
         if (rc2) return rc2;
-        a.part_cnt = static_cast<int32_t*>(ctx->d_work);
+        a.part_cnt = static_cast<int32_t*>(ctx->work.p);
         a.part_first = a.part_cnt + n;
         a.parts = P;
         const dim3 g((unsigned)(M * P));

@@ -10,14 +10,23 @@
 
 #include "../../include/orloj.h"
 
+// A scratch block of a context, grown on demand.
+struct orloj_block {
+    void* p;
+    size_t bytes;
+};
+
 struct orloj_ctx {
     int device;
     int n_cu;        // compute units of the device
     hipStream_t stream;
     int* d_err;      // device status word (data error bits)
     float* d_fill;   // stand-in table entries: 16 zeros, 16 ones
-    void* d_work;    // scratch of the affine scorer (grown on demand), or NULL
-    size_t work_bytes;
+    // Scratch.  A block's growth frees the old one, which a captured graph may
+    // still name, so each use has a block that only its own larger calls grow.
+    orloj_block work;  // emax_kernel's sums; iterate_kernel's split drop phase
+    orloj_block esum;  // turned_esum_kernel's sums
+    orloj_block mix;   // laws_mix_kernel's powers (never used under capture)
     float* noalloc_scratch;   // this device's fixed scratch array (NULL: unavailable)
     hipError_t noalloc_err;   // why it is unavailable
     char msg[512];

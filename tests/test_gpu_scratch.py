@@ -1,0 +1,100 @@
+"""The context's scratch blocks under HIP graph capture: a captured call does not
+lose its scratch to later calls of other kinds, and a call whose scratch cannot
+grow because its stream is under capture takes the path that does without."""
+import numpy as np
+import pytest
+import torch
+
+import oracle
+import parity
+from paper_2209_00159_amd import orloj as O
+from paper_2209_00159_amd import workloads as W
+
+pytestmark = pytest.mark.gpu
+
+
+def captured(stream, call):
+    torch.cuda.synchronize()
+    g = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(g, stream=stream):
+        call()
+    return g
+
+
+def replay_and_compare(g, sc, wl, stream, ora):
+    for buf in (sc.finish_prob, sc.expected_finish, sc.expected_latency, sc.score_out):
+        buf.fill_(-7.0)
+    torch.cuda.synchronize()
+    g.replay()
+    torch.cuda.synchronize()
+    with torch.cuda.stream(stream):
+        sc.select()
+        sc.ctx.sync()
+    parity.compare(wl, sc.fetch(), ora)
+
+
+def few_queues(n_models, seed):
+    """The first model's queue holds 40 requests, the others none."""
+    return W.random_affine(seed, n_models=n_models, n_classes=8, n_bins=600,
+                           batch_sizes=(5, 17, 40), queue_lens=[40] + [0] * (n_models - 1))
+
+
+@pytest.mark.parametrize("warm", ["same call", "larger launch"])
+def test_captured_affine_call(warm):
+    print("scratch", warm, flush=True)
+    stream = torch.cuda.Stream()
+    ctx = O.Context(stream=stream)
+    n = 200                                    # x 3 batch sizes: more pairs than turned_kernel takes
+    wl = few_queues(n, 7)
+    many = W.random_affine(8, n_models=n, n_classes=8, n_bins=600, batch_sizes=(5, 17, 40),
+                           queue_lens=[40] * n)
+    sc, big = O.Scorer(wl, ctx), O.Scorer(many, ctx)
+    torch.cuda.synchronize()
+    sc.build()
+    # turned_kernel's block is there ("same call") or only emax_kernel's is
+    (sc if warm == "same call" else big).run()
+    g = captured(stream, sc.score)
+    ora = oracle.score_workload_affine(wl, wl.c0_ms, wl.c1)
+    replay_and_compare(g, sc, wl, stream, ora)
+    # eager work of other kinds, each with more scratch than the one before
+    laws = W.random_case(9, n_models=1, n_classes=16, n_bins=8192, queue_lens=[0],
+                         batch_sizes=tuple(range(1, 65)))
+    it = O.Iterator(laws, ctx)
+    torch.cuda.synchronize()
+    it.build()
+    if warm == "same call":
+        big.run()
+    ctx.sync()
+    junk = torch.full((1 << 22,), 3.0, device="cuda")  # takes freed memory, if any
+    for _ in range(3):
+        replay_and_compare(g, sc, wl, stream, ora)
+    assert float(junk.min()) == 3.0 and float(junk.max()) == 3.0
+
+
+def test_captured_model_laws_use_no_scratch():
+    stream = torch.cuda.Stream()
+    ctx = O.Context(stream=stream)
+    wl = W.random_case(11, n_models=1, n_classes=9, n_bins=700, queue_lens=[0], batch_sizes=(1, 4))
+    it = O.Iterator(wl, ctx)
+    torch.cuda.synchronize()
+    it.build()
+    ctx.sync()
+    want = [t.cpu().numpy() for t in (it.law, it.disc, it.model_el)]
+    g = captured(stream, it.build)
+    larger = W.random_case(12, n_models=2, n_classes=9, n_bins=4096, queue_lens=[0, 0],
+                           batch_sizes=tuple(range(1, 33)))
+    other = O.Iterator(larger, ctx)
+    torch.cuda.synchronize()
+    other.build()
+    ctx.sync()
+    for _ in range(3):
+        for t in (it.law, it.disc, it.model_el):
+            t.fill_(-7.0)
+        torch.cuda.synchronize()
+        g.replay()
+        torch.cuda.synchronize()
+        got = [t.cpu().numpy() for t in (it.law, it.disc, it.model_el)]
+        for a, b in zip(got[:2], want[:2]):
+            assert np.array_equal(a.view(np.uint8), b.view(np.uint8))
+        # an fp64 sum in another order, rounded to fp32 once
+        assert np.allclose(got[2], want[2], rtol=2.0**-23, atol=0)
