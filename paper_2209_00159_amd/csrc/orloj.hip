@@ -2400,6 +2400,12 @@ namespace {
 // d = e^{-b w}: an in-thread fp64 prefix, a weighted DPP scan across the
 // wave and a weighted combination across the four waves.  Block 0 of each
 // model also writes the model-wide E[L] of F_mix^s (§4.3).
+//
+// Bound by HBM: the table is read twice and two tables are written.  The next
+// class's row is loaded while a class is worked on (the classes are a serial
+// chain of loads and a barrier otherwise), and the rows leave in whole lines,
+// turned in LDS.  Tables and laws of 32 models x 64 batch sizes x 32 classes x
+// 4096 bins, us: 1425 before, 1374 with the row loaded ahead, 1248 with both.
 // ---------------------------------------------------------------------------
 struct LawArgs {
     const float* tab;          // [M][nbs][C][K] 1 - F(x_{k+1})
@@ -2440,6 +2446,27 @@ __device__ __forceinline__ void load_cdf_chunk(double (&F)[VPT], const float* __
     for (int j = 0; j < VPT; ++j) F[j] = base + j < K ? 1.0 - (double)t[base + j] : 1.0;
 }
 
+// One thread's VPT consecutive entries of a row as they are (0 past its end:
+// F = 1), with load_cdf_chunk's accesses.
+template <int VPT>
+__device__ __forceinline__ void load_row_chunk(float (&v)[VPT], const float* __restrict__ t, int base,
+                                               int K) {
+    if constexpr (VPT % 4 == 0) {
+        if ((K & 3) == 0) {
+#pragma unroll
+            for (int j = 0; j < VPT; j += 4) {
+                const bool in = base + j < K;
+                const float4 x = in ? *reinterpret_cast<const float4*>(t + base + j)
+                                    : make_float4(0.0f, 0.0f, 0.0f, 0.0f);
+                v[j] = x.x; v[j + 1] = x.y; v[j + 2] = x.z; v[j + 3] = x.w;
+            }
+            return;
+        }
+    }
+#pragma unroll
+    for (int j = 0; j < VPT; ++j) v[j] = base + j < K ? t[base + j] : 0.0f;
+}
+
 // Store one thread's VPT entries (those below K) of a row.
 template <int VPT>
 __device__ __forceinline__ void store_chunk(float* __restrict__ o, const float (&v)[VPT], int base, int K) {
@@ -2457,9 +2484,42 @@ __device__ __forceinline__ void store_chunk(float* __restrict__ o, const float (
         if (base + j < K) o[base + j] = v[j];
 }
 
+// store_chunk for a wave's lanes together: with more than four entries a lane,
+// the lanes' float4s lie 4 VPT bytes apart; turned in LDS, a store writes 1 KB
+// of the row.  Rows of LDS are padded by a float4 against bank conflicts.
+template <int VPT>
+constexpr int kTurnedRow = VPT % 4 == 0 && VPT > 4 ? VPT + 4 : 0;
+
+template <int VPT>
+__device__ __forceinline__ void store_row(float* __restrict__ o, const float (&v)[VPT], int base, int K,
+                                          float* turn) {
+    if constexpr (kTurnedRow<VPT> != 0) {
+        if ((K & 3) == 0) {
+            constexpr int P = VPT / 4;
+            const int lane = threadIdx.x & 63, first = base - lane * VPT;
+#pragma unroll
+            for (int j = 0; j < VPT; j += 4)
+                *reinterpret_cast<float4*>(turn + lane * kTurnedRow<VPT> + j) =
+                    make_float4(v[j], v[j + 1], v[j + 2], v[j + 3]);
+            wave_lds_fence();
+#pragma unroll
+            for (int i = 0; i < P; ++i) {
+                const int f = 64 * i + lane;
+                const float4 x =
+                    *reinterpret_cast<const float4*>(turn + f / P * kTurnedRow<VPT> + f % P * 4);
+                if (first + 4 * f < K) *reinterpret_cast<float4*>(o + first + 4 * f) = x;
+            }
+            wave_lds_fence();
+            return;
+        }
+    }
+    store_chunk<VPT>(o, v, base, K);
+}
+
 template <int VPT>
 __global__ __launch_bounds__(kThreads) void laws_kernel(const LawArgs a) {
-    __shared__ float s_wave[kWaves];
+    __shared__ float s_wave[2][kWaves];   // of a class, by its parity
+    __shared__ __align__(16) float s_turn[kWaves][kTurnedRow<VPT> ? 64 * kTurnedRow<VPT> : 4];
     __shared__ double s_el[kWaves];
     const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
     const int q = (int)(blockIdx.x / (unsigned)a.nbs);
@@ -2519,25 +2579,27 @@ __global__ __launch_bounds__(kThreads) void laws_kernel(const LawArgs a) {
     const float w31 = exp2_hw(log2d * (float)(VPT * (lane >= 32 ? lane - 31 : 0)));
     const float d_wave = exp2_hw(log2d * (float)(64 * VPT));
 
+    float t[VPT];   // the next class's row, loaded while a class is worked on
+    load_row_chunk<VPT>(t, a.tab + row0 * (size_t)K, base, K);
     for (int c = 0; c < C; ++c) {
         const size_t r = (row0 + (size_t)c) * (size_t)K;
         double g[VPT];
-        load_cdf_chunk<VPT>(g, a.tab + r, base, K);
         double z = 0.0;
 #pragma unroll
+        for (int j = 0; j < VPT; ++j) g[j] = (1.0 - (double)t[j]) * pm[j];
+        if (c + 1 < C) load_row_chunk<VPT>(t, a.tab + r + K, base, K);
+#pragma unroll
         for (int j = 0; j < VPT; ++j) {
-            g[j] *= pm[j];
             z = fma(z, d, g[j]);
         }
         // in-wave weighted scan of the chunk totals, then across the waves
         const float A = wave_wscan((float)z, rp, w15, w31);
-        if (lane == 63) s_wave[wv] = A;
+        if (lane == 63) s_wave[c & 1][wv] = A;
         __syncthreads();
         float carry = 0.0f;   // discounted sum of the earlier waves' bins, at the end of the last one
 #pragma unroll
         for (int i = 0; i < kWaves; ++i)
-            if (i < wv) carry = fmaf(carry, d_wave, s_wave[i]);
-        __syncthreads();
+            if (i < wv) carry = fmaf(carry, d_wave, s_wave[c & 1][i]);
         // prefix up to the end of the previous thread chunk
         const float prev = __shfl_up(A, 1, 64);
         const float before = (lane > 0 ? prev : 0.0f) + carry * exp2_hw(log2d * (float)(VPT * lane));
@@ -2549,8 +2611,8 @@ __global__ __launch_bounds__(kThreads) void laws_kernel(const LawArgs a) {
             lv[j] = (float)g[j];
             dv[j] = (float)zz;
         }
-        store_chunk<VPT>(a.law + r, lv, base, K);
-        store_chunk<VPT>(a.disc + r, dv, base, K);
+        store_row<VPT>(a.law + r, lv, base, K, s_turn[wv]);
+        store_row<VPT>(a.disc + r, dv, base, K, s_turn[wv]);
     }
 }
 
