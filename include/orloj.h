@@ -330,9 +330,9 @@ int orloj_select_batch(orloj_ctx *ctx, const orloj_grid *grid, const orloj_queue
  * orloj_score_candidates.  A queue longer than 1024 requests, when there are
  * few enough models (4 M <= the GPU's compute units), has its drop phase run
  * in parts of 256 requests: the per-part counts (M x parts x |S| x 8 bytes)
- * go to the context's scratch block, grown on demand as for the affine
- * scorer (ORLOJ_E_NOMEM if that fails).  d_support entries are taken to lie
- * in [0, K), as orloj_build_cdfs writes them.
+ * go to a scratch block of the context that nothing else uses, grown on demand
+ * as for the affine scorer (ORLOJ_E_NOMEM if that fails).  d_support entries
+ * are taken to lie in [0, K), as orloj_build_cdfs writes them.
  */
 /*
  * Piecewise-step cost functions (App. B) for orloj_iterate: request r's cost

@@ -3520,7 +3520,7 @@ int orloj_create(orloj_ctx** out, int32_t hip_device, void* hip_stream) {
     ctx->stream = (hipStream_t)hip_stream;
     ctx->d_err = nullptr;
     ctx->d_fill = nullptr;
-    ctx->work = ctx->esum = ctx->mix = orloj_block{nullptr, 0};
+    ctx->work = ctx->drop = ctx->esum = ctx->mix = orloj_block{nullptr, 0};
     ctx->noalloc_scratch = nullptr;
     ctx->noalloc_err = hipSuccess;
     ctx->msg[0] = 0;
@@ -3557,7 +3557,7 @@ void orloj_destroy(orloj_ctx* ctx) {
     (void)hipStreamSynchronize(ctx->stream);
     if (ctx->d_err) (void)hipFree(ctx->d_err);
     if (ctx->d_fill) (void)hipFree(ctx->d_fill);
-    for (const orloj_block& b : {ctx->work, ctx->esum, ctx->mix})
+    for (const orloj_block& b : {ctx->work, ctx->drop, ctx->esum, ctx->mix})
         if (b.p) (void)hipFree(b.p);
     delete ctx;
 }
@@ -3570,7 +3570,7 @@ int orloj_set_score_chunk(orloj_ctx* ctx, int32_t steps) {
 
 int orloj_set_stream(orloj_ctx* ctx, void* hip_stream) {
     if (!ctx) return ORLOJ_E_INVALID;
-    if ((hipStream_t)hip_stream != ctx->stream && (ctx->work.p || ctx->esum.p || ctx->mix.p)) {
+    if ((hipStream_t)hip_stream != ctx->stream && (ctx->work.p || ctx->drop.p || ctx->esum.p || ctx->mix.p)) {
         // calls still queued on the old stream may use the scratch
         hipError_t e = hipSetDevice(ctx->device);
         if (e == hipSuccess) e = hipStreamSynchronize(ctx->stream);
@@ -4172,9 +4172,9 @@ int orloj_iterate(orloj_ctx* ctx, const orloj_grid* grid, const int32_t* d_suppo
     if (longest > kIterWideQueue && 4 * (int64_t)M <= n_cu) {
         const int P = (int)((longest + kDropPart - 1) / kDropPart);
         const size_t n = (size_t)M * (size_t)P * (size_t)a.nbs;
-        int rc2 = ensure_block(ctx, &ctx->work, 2 * n * sizeof(int32_t));
+        int rc2 = ensure_block(ctx, &ctx->drop, 2 * n * sizeof(int32_t));
         if (rc2) return rc2;
-        a.part_cnt = static_cast<int32_t*>(ctx->work.p);
+        a.part_cnt = static_cast<int32_t*>(ctx->drop.p);
         a.part_first = a.part_cnt + n;
         a.parts = P;
         const dim3 g((unsigned)(M * P));

@@ -98,3 +98,52 @@ def test_captured_model_laws_use_no_scratch():
             assert np.array_equal(a.view(np.uint8), b.view(np.uint8))
         # an fp64 sum in another order, rounded to fp32 once
         assert np.allclose(got[2], want[2], rtol=2.0**-23, atol=0)
+
+
+@pytest.mark.parametrize("kept", ["affine sums", "drop phase"])
+def test_scoring_and_iteration_grow_blocks_of_their_own(kept):
+    """A captured affine call whose sums lie in emax_kernel's block replays after an
+    iteration of long queues has grown its scratch past them, and a captured
+    iteration after a larger affine call."""
+    print("scratch of scoring and iteration", kept, flush=True)
+    stream = torch.cuda.Stream()
+    ctx = O.Context(stream=stream)
+
+    def scorer(n):                             # 3 n pairs: score_kernel and emax_kernel
+        wl = W.random_affine(21, n_models=n, n_classes=4, n_bins=300, batch_sizes=(5, 17, 40),
+                             queue_lens=[40] * n)
+        return wl, O.Scorer(wl, ctx)
+
+    def iterator(n, queue, sizes):
+        return O.Iterator(W.random_case(22, n_models=n, n_classes=4, n_bins=64, batch_sizes=sizes,
+                                        queue_lens=[queue] * n, tau_range=(0.0, 90.0)), ctx)
+
+    if kept == "affine sums":                  # 200 x 2 x 40 sums against 8 x 16 x 140 x 8 bytes
+        (wl, sc), other = scorer(200), iterator(8, 4096, tuple(range(1, 141)))
+        torch.cuda.synchronize()
+        sc.run()
+        g = captured(stream, sc.score)
+        ora = oracle.score_workload_affine(wl, wl.c0_ms, wl.c1)
+
+        def replay():
+            replay_and_compare(g, sc, wl, stream, ora)
+    else:
+        it, other = iterator(1, 1100, (1, 8)), scorer(600)[1]
+        torch.cuda.synchronize()
+        want = it.run()
+        g = captured(stream, it.iterate)
+
+        def replay():
+            for t in (it.timed_out, it.score, it.cand_bs, it.batch):
+                t.fill_(-7)
+            torch.cuda.synchronize()
+            g.replay()
+            for k, v in it.fetch().items():
+                assert np.array_equal(v.view(np.uint8), want[k].view(np.uint8)), k
+
+    replay()
+    other.run()
+    junk = torch.full((1 << 22,), 3.0, device="cuda")  # takes freed memory, if any
+    for _ in range(3):
+        replay()
+    assert float(junk.min()) == 3.0 and float(junk.max()) == 3.0
