@@ -223,14 +223,14 @@ int orloj_score_candidates(orloj_ctx *ctx, const orloj_grid *grid, const float *
  * error (orloj_sync); that model's requests then score as dead.
  * The sums of 1 - G behind E[X] do not depend on the batch size, so they
  * are formed once per (model, prefix length) into a scratch block the
- * context owns (M x ceil(K / 256) x the longest prefix floats, doubles where
- * that is at most 2^19 sums and the launch is small; the doubles have a block
- * of their own, and a call that cannot have it, for want of memory or because
- * its stream is under capture, uses the floats).  The
- * first call that needs a larger block waits for the context's
- * stream, frees the old block and allocates the new one (ORLOJ_E_NOMEM if
- * that fails); the block is reused by later calls and freed by
- * orloj_destroy.  Calls on one context are ordered by its stream.
+ * context owns: n = M x ceil(K / 256) x the longest prefix sums, max(4 n,
+ * min(8 n, 2^22)) bytes (small launches hold the sums as doubles, larger ones
+ * as floats).  The first call that needs a larger block waits for the
+ * context's stream, frees the old block and allocates the new one
+ * (ORLOJ_E_NOMEM if that fails); the block is reused by later calls and freed
+ * by orloj_destroy.  A stream under capture cannot grow it: make a call of
+ * the same grid and longest prefix before the capture.  Calls on one context
+ * are ordered by its stream.
  */
 int orloj_score_candidates_affine(orloj_ctx *ctx, const orloj_grid *grid, const float *d_ccdf,
                                   const int32_t *d_support, const double *d_c0_ms,

@@ -1533,6 +1533,9 @@ __global__ __launch_bounds__(64) void emax_kernel(const ScoreArgs a) {
 constexpr int kTurnWaves = 8;                   // waves of a workgroup
 constexpr int kETile = 128;                     // bins of an E tile: two per lane
 constexpr int kPanel = 256;                     // bins of one affine E sum
+// most affine E sums turned_esum_kernel writes: doubles that the fixed scratch
+// array holds, so that the allocation-free call takes the same kernels
+constexpr int64_t kTurnedSums = ORLOJ_NOALLOC_SCRATCH_FLOATS / 2;
 constexpr int kGtRow = 136;                     // bytes of a turned row: 16 fp64, padded
 constexpr int kERow = 640;                      // bytes of a row of lane sums: 64 fp64, padded
 constexpr int kTriBytes = 64 * 65 / 2 * 4;      // a block's P when no prefix is longer than 64
@@ -3520,7 +3523,7 @@ int orloj_create(orloj_ctx** out, int32_t hip_device, void* hip_stream) {
     ctx->stream = (hipStream_t)hip_stream;
     ctx->d_err = nullptr;
     ctx->d_fill = nullptr;
-    ctx->work = ctx->drop = ctx->esum = ctx->mix = orloj_block{nullptr, 0};
+    ctx->work = ctx->drop = ctx->mix = orloj_block{nullptr, 0};
     ctx->noalloc_scratch = nullptr;
     ctx->noalloc_err = hipSuccess;
     ctx->msg[0] = 0;
@@ -3557,7 +3560,7 @@ void orloj_destroy(orloj_ctx* ctx) {
     (void)hipStreamSynchronize(ctx->stream);
     if (ctx->d_err) (void)hipFree(ctx->d_err);
     if (ctx->d_fill) (void)hipFree(ctx->d_fill);
-    for (const orloj_block& b : {ctx->work, ctx->drop, ctx->esum, ctx->mix})
+    for (const orloj_block& b : {ctx->work, ctx->drop, ctx->mix})
         if (b.p) (void)hipFree(b.p);
     delete ctx;
 }
@@ -3570,7 +3573,7 @@ int orloj_set_score_chunk(orloj_ctx* ctx, int32_t steps) {
 
 int orloj_set_stream(orloj_ctx* ctx, void* hip_stream) {
     if (!ctx) return ORLOJ_E_INVALID;
-    if ((hipStream_t)hip_stream != ctx->stream && (ctx->work.p || ctx->drop.p || ctx->esum.p || ctx->mix.p)) {
+    if ((hipStream_t)hip_stream != ctx->stream && (ctx->work.p || ctx->drop.p || ctx->mix.p)) {
         // calls still queued on the old stream may use the scratch
         hipError_t e = hipSetDevice(ctx->device);
         if (e == hipSuccess) e = hipStreamSynchronize(ctx->stream);
@@ -3763,8 +3766,7 @@ int score_common(orloj_ctx* ctx, const orloj_grid* grid, const float* d_ccdf,
     if (nblk > 0x7fffffff) return orloj_ctx_fail(ctx, ORLOJ_E_UNSUPPORTED, "too many (model, batch size) pairs");
 
     // Launches too small to fill the chip go to turned_kernel (its row offsets
-    // are 32-bit; its E sums are doubles, and must fit the fixed scratch for
-    // every call that the float sums do).  score_kernel takes about as long
+    // are 32-bit).  score_kernel takes about as long
     // for one pair as for a full chip, turned_kernel's time grows with the
     // pairs past one workgroup per compute unit, so the line lies where they
     // meet: score + selection, us, score_kernel / turned_kernel, at
@@ -3775,21 +3777,33 @@ int score_common(orloj_ctx* ctx, const orloj_grid* grid, const float* d_ccdf,
     const int simds = 4 * (ctx->n_cu > 0 ? ctx->n_cu : 256);
     const bool longest = maxcap == 64 && grid->n_bins >= 1024;
     const int64_t np_t = (grid->n_bins + kPanel - 1) / kPanel;
-    bool turned = active <= (longest ? simds : simds / 2) &&
-                  (int64_t)grid->n_classes * grid->n_bins <= 0x3fffffff &&
-                  (!d_c1 || (int64_t)M * np_t * maxcap <= ORLOJ_NOALLOC_SCRATCH_FLOATS / 2);
-    if (turned && d_c1 && !fixed_psum) {
-        // where the doubles cannot be had (a stream under capture whose block
-        // is too small, no memory left), score_kernel's float sums may be there
-        const size_t need = (size_t)M * (size_t)np_t * (size_t)maxcap * sizeof(double);
-        if (need > ctx->esum.bytes && capturing(ctx)) {
-            turned = false;
+    const bool turned = active <= (longest ? simds : simds / 2) &&
+                        (int64_t)grid->n_classes * grid->n_bins <= 0x3fffffff &&
+                        (!d_c1 || (int64_t)M * np_t * maxcap <= kTurnedSums);
+    // Affine mode: the sums of 1 - G, [M][panels][maxcap], floats of
+    // emax_kernel or doubles of turned_esum_kernel.  The block is sized for
+    // either, from the number of sums alone, so that whichever queues were
+    // filled in an earlier call of a grid, a later one finds its block there
+    // (a stream under capture cannot grow it).
+    float* psum = fixed_psum;
+    if (d_c1) {
+        if ((int64_t)M * panels > 0x7fffffff)
+            return orloj_ctx_fail(ctx, ORLOJ_E_UNSUPPORTED, "too many (model, panel) pairs");
+        const int64_t need = (int64_t)M * std::max<int64_t>(panels, np_t) * maxcap;
+        if (fixed_psum) {
+            if ((uint64_t)need > fixed_floats)
+                return orloj_ctx_fail(ctx, ORLOJ_E_UNSUPPORTED,
+                                      "the call needs %lld scratch floats (models x panels x longest "
+                                      "prefix), the fixed scratch holds %zu",
+                                      (long long)need, fixed_floats);
         } else {
             hipError_t e = hipSetDevice(ctx->device);
             if (e != hipSuccess) return hip_fail(ctx, e, "hipSetDevice");
-            rc = ensure_block(ctx, &ctx->esum, need);
-            if (rc && rc != ORLOJ_E_NOMEM) return rc;
-            turned = rc == ORLOJ_OK;
+            rc = ensure_block(ctx, &ctx->work,
+                              std::max((size_t)need * sizeof(float),
+                                       (size_t)std::min(need, kTurnedSums) * sizeof(double)));
+            if (rc) return rc;
+            psum = (float*)ctx->work.p;
         }
     }
     if (turned) {
@@ -3830,7 +3844,7 @@ int score_common(orloj_ctx* ctx, const orloj_grid* grid, const float* d_ccdf,
         a.esum = nullptr;
         a.np_e = 0;
         if (d_c1) {
-            a.esum = (double*)(fixed_psum ? (void*)fixed_psum : ctx->esum.p);
+            a.esum = (double*)(void*)psum;
             a.np_e = (int)np_t;
         }
         e = launch_turned(a, ctx->stream);
@@ -3877,25 +3891,9 @@ int score_common(orloj_ctx* ctx, const orloj_grid* grid, const float* d_ccdf,
     a.psum = nullptr;
     a.np_e = 0;
     if (d_c1) {
-        // emax_kernel's panel sums, formed first: [M][panels][maxcap] floats,
-        // on the score waves' own panels
-        const int64_t np = panels;
-        if ((int64_t)M * np > 0x7fffffff)
-            return orloj_ctx_fail(ctx, ORLOJ_E_UNSUPPORTED, "too many (model, panel) pairs");
-        const size_t need = (size_t)M * (size_t)np * (size_t)maxcap;
-        if (fixed_psum) {
-            if (need > fixed_floats)
-                return orloj_ctx_fail(ctx, ORLOJ_E_UNSUPPORTED,
-                                      "the call needs %zu scratch floats (models x panels x longest "
-                                      "prefix), the fixed scratch holds %zu",
-                                      need, fixed_floats);
-            a.psum = fixed_psum;
-        } else {
-            rc = ensure_block(ctx, &ctx->work, need * sizeof(float));
-            if (rc) return rc;
-            a.psum = (float*)ctx->work.p;
-        }
-        a.np_e = (int)np;
+        // emax_kernel's panel sums, formed first, on the score waves' own panels
+        a.psum = psum;
+        a.np_e = panels;
         switch (cpl) {
             case 1: e = launch_emax<1>(a, ctx->stream); break;
             case 2: e = launch_emax<2>(a, ctx->stream); break;

@@ -24,9 +24,8 @@ struct orloj_ctx {
     float* d_fill;   // stand-in table entries: 16 zeros, 16 ones
     // Scratch.  A block's growth frees the old one, which a captured graph may
     // still name, so each use has a block that only its own larger calls grow.
-    orloj_block work;  // emax_kernel's sums
+    orloj_block work;  // the affine scorer's sums (emax_kernel, turned_esum_kernel)
     orloj_block drop;  // iterate_kernel's split drop phase
-    orloj_block esum;  // turned_esum_kernel's sums
     orloj_block mix;   // laws_mix_kernel's powers (never used under capture)
     float* noalloc_scratch;   // this device's fixed scratch array (NULL: unavailable)
     hipError_t noalloc_err;   // why it is unavailable

@@ -1,6 +1,6 @@
 """The context's scratch blocks under HIP graph capture: a captured call does not
-lose its scratch to later calls of other kinds, and a call whose scratch cannot
-grow because its stream is under capture takes the path that does without."""
+lose its scratch to later calls of other kinds, and finds it whichever queues were
+filled in the calls before."""
 import numpy as np
 import pytest
 import torch
@@ -44,14 +44,14 @@ def test_captured_affine_call(warm):
     print("scratch", warm, flush=True)
     stream = torch.cuda.Stream()
     ctx = O.Context(stream=stream)
-    n = 200                                    # x 3 batch sizes: more pairs than turned_kernel takes
+    n = 200
     wl = few_queues(n, 7)
     many = W.random_affine(8, n_models=n, n_classes=8, n_bins=600, batch_sizes=(5, 17, 40),
                            queue_lens=[40] * n)
     sc, big = O.Scorer(wl, ctx), O.Scorer(many, ctx)
     torch.cuda.synchronize()
     sc.build()
-    # turned_kernel's block is there ("same call") or only emax_kernel's is
+    # the affine sums' block is as large for few filled queues as for many
     (sc if warm == "same call" else big).run()
     g = captured(stream, sc.score)
     ora = oracle.score_workload_affine(wl, wl.c0_ms, wl.c1)
@@ -69,6 +69,42 @@ def test_captured_affine_call(warm):
     for _ in range(3):
         replay_and_compare(g, sc, wl, stream, ora)
     assert float(junk.min()) == 3.0 and float(junk.max()) == 3.0
+
+
+@pytest.mark.parametrize("warm", ["one queue filled", "every queue filled"])
+def test_affine_bits_do_not_depend_on_the_scratch(warm):
+    """A call warmed by another number of filled queues of the same grid can be
+    captured, and has the bits of the eager and of the allocation-free call."""
+    print("affine bits", warm, flush=True)
+    n = 200
+    few = few_queues(n, 7)
+    many = W.random_affine(8, n_models=n, n_classes=8, n_bins=600, batch_sizes=(5, 17, 40),
+                           queue_lens=[40] * n)
+    first, wl = (few, many) if warm == "one queue filled" else (many, few)
+    stream = torch.cuda.Stream()
+    ctx = O.Context(stream=stream)
+    a, b = O.Scorer(first, ctx), O.Scorer(wl, ctx)
+    torch.cuda.synchronize()
+    a.run()
+    b.build()
+    g = captured(stream, b.score)
+
+    def outputs(call):
+        for buf in (b.finish_prob, b.expected_finish, b.expected_latency, b.score_out):
+            buf.fill_(-7.0)
+        torch.cuda.synchronize()
+        call()
+        torch.cuda.synchronize()
+        with torch.cuda.stream(stream):
+            b.select()
+            ctx.sync()
+        return b.fetch()
+
+    got = outputs(g.replay)
+    parity.compare(wl, got, oracle.score_workload_affine(wl, wl.c0_ms, wl.c1))
+    for call in (b.score, lambda: b.score(noalloc=True), g.replay):
+        for k, v in outputs(call).items():
+            assert np.array_equal(v.view(np.uint8), got[k].view(np.uint8)), k
 
 
 def test_captured_model_laws_use_no_scratch():
