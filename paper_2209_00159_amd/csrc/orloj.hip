@@ -2419,6 +2419,7 @@ struct LawArgs {
     float* model_el;           // [M][nbs]
     int* err;
     double* pm;                // laws_mix_kernel: [pairs][K] F_mix^(s-1)
+    int vshift;                // laws_mix_kernel: log2 of laws_kernel's bins per thread
     double b;
     int M, C, K, nbs;
     int bs[ORLOJ_MAX_BATCH_SIZES];
@@ -2561,7 +2562,7 @@ __global__ __launch_bounds__(kThreads) void laws_kernel(const LawArgs a) {
 #pragma unroll
     for (int j = 0; j < VPT; ++j) {
         pm[j] = s > 1 ? pow(mix[j], (double)(s - 1)) : 1.0;
-        if (base + j < K) el += 1.0 - pm[j] * mix[j];
+        if (base + j < K) el += fma(-pm[j], mix[j], 1.0);
     }
     // model-wide E[L] = w (1/2 + sum_k (1 - F_mix^s(x_{k+1})))
     for (int o = 32; o > 0; o >>= 1) el += __shfl_xor(el, o, 64);
@@ -2636,7 +2637,10 @@ constexpr int kMixThreads = 1024;
 template <bool VEC>
 __global__ __launch_bounds__(kMixThreads) void laws_mix_kernel(const LawArgs a) {
     constexpr int V = VEC ? 4 : 1;
-    __shared__ double s_el[kMixThreads / 64];
+    // each bin's 1 - F_mix^s; an entry's gap after each of laws_kernel's chunks
+    // against bank conflicts
+    extern __shared__ __align__(16) double s_bin[];
+    __shared__ double s_el[kWaves];
     const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
     const int pair = (int)blockIdx.x;
     const int q = pair / a.nbs;
@@ -2655,7 +2659,6 @@ __global__ __launch_bounds__(kMixThreads) void laws_mix_kernel(const LawArgs a) 
         if (tid == 0) atomicOr(a.err, kErrWeights);
         wsum = 1.0;
     }
-    double el = 0.0;
     for (int base = V * tid; base < K; base += V * (int)blockDim.x) {
         double mix[V];
 #pragma unroll
@@ -2678,7 +2681,7 @@ __global__ __launch_bounds__(kMixThreads) void laws_mix_kernel(const LawArgs a) 
 #pragma unroll
         for (int j = 0; j < V; ++j) {
             pm[j] = s > 1 ? pow(mix[j], (double)(s - 1)) : 1.0;
-            el += 1.0 - pm[j] * mix[j];
+            s_bin[base + j + ((base + j) >> a.vshift)] = fma(-pm[j], mix[j], 1.0);
         }
         double* o = a.pm + (size_t)pair * (size_t)K + base;
         if constexpr (VEC) {
@@ -2688,15 +2691,38 @@ __global__ __launch_bounds__(kMixThreads) void laws_mix_kernel(const LawArgs a) 
             o[0] = pm[0];
         }
     }
-    // model-wide E[L] = w (1/2 + sum_k (1 - F_mix^s(x_{k+1})))
-    for (int o = 32; o > 0; o >>= 1) el += __shfl_xor(el, o, 64);
-    if (lane == 0) s_el[wv] = el;
+    // model-wide E[L] = w (1/2 + sum_k (1 - F_mix^s(x_{k+1}))), summed in the
+    // order of laws_kernel's threads and waves: the same bits
+    __syncthreads();
+    for (int u = wv; u < kWaves; u += (int)blockDim.x / 64) {
+        const int t = 64 * u + lane, first = t << a.vshift;
+        const int n = min(1 << a.vshift, K - first);
+        double el = 0.0;
+        for (int j = 0; j < n; ++j) el += s_bin[first + t + j];
+        for (int o = 32; o > 0; o >>= 1) el += __shfl_xor(el, o, 64);
+        if (lane == 0) s_el[u] = el;
+    }
     __syncthreads();
     if (tid == 0) {
         double tot = 0.0;
-        for (int i = 0; i < (int)blockDim.x / 64; ++i) tot += s_el[i];
+        for (int i = 0; i < kWaves; ++i) tot += s_el[i];
         a.model_el[pair] = (float)(w * (0.5 + tot));
     }
+}
+
+template <bool VEC>
+hipError_t launch_laws_mix(const LawArgs& a, unsigned pairs, int threads, hipStream_t st) {
+    const int lds = (int)sizeof(double) * (a.K + (a.K >> a.vshift) + 1);
+    static std::atomic<int> allowed{60 * 1024};   // per template instance; device-independent
+    if (lds > allowed.load(std::memory_order_relaxed)) {
+        constexpr int most = (int)sizeof(double) * (ORLOJ_MAX_BINS + kThreads + 1);
+        const hipError_t e = hipFuncSetAttribute((const void*)laws_mix_kernel<VEC>,
+                                                 hipFuncAttributeMaxDynamicSharedMemorySize, most);
+        if (e != hipSuccess) return e;
+        allowed.store(most, std::memory_order_relaxed);
+    }
+    hipLaunchKernelGGL(laws_mix_kernel<VEC>, dim3(pairs), dim3(threads), lds, st, a);
+    return hipGetLastError();
 }
 
 template <int VPT>
@@ -3349,6 +3375,10 @@ int chunk_per_lane(int K) {
     return c;
 }
 
+// Most (model, batch size) pairs whose laws are formed by laws_mix_kernel and
+// laws_row_kernel.
+int64_t law_split_pairs(const orloj_ctx* ctx) { return ctx->n_cu > 0 ? ctx->n_cu : 256; }
+
 
 template <int CPL, bool EXACT, int CR, bool AFF>
 hipError_t launch_score_v(const ScoreArgs& a, unsigned grid, hipStream_t st) {
@@ -3524,6 +3554,7 @@ int orloj_create(orloj_ctx** out, int32_t hip_device, void* hip_stream) {
     ctx->d_err = nullptr;
     ctx->d_fill = nullptr;
     ctx->work = ctx->drop = ctx->mix = orloj_block{nullptr, 0};
+    ctx->mix_used = false;
     ctx->noalloc_scratch = nullptr;
     ctx->noalloc_err = hipSuccess;
     ctx->msg[0] = 0;
@@ -3544,6 +3575,15 @@ int orloj_create(orloj_ctx** out, int32_t hip_device, void* hip_stream) {
     // the allocation-free scorer's scratch on this device (its failure only
     // disables that entry point)
     if (e == hipSuccess) ctx->noalloc_scratch = scratch_address(hip_device, &ctx->noalloc_err);
+    if (e == hipSuccess) {
+        const size_t bytes = (size_t)law_split_pairs(ctx) * ORLOJ_MAX_BINS * sizeof(double);
+        if (hipMalloc(&ctx->mix.p, bytes) == hipSuccess) {
+            ctx->mix.bytes = bytes;
+        } else {
+            ctx->mix.p = nullptr;   // laws_kernel does without
+            (void)hipGetLastError();
+        }
+    }
     if (e != hipSuccess) {
         if (ctx->d_err) (void)hipFree(ctx->d_err);
         if (ctx->d_fill) (void)hipFree(ctx->d_fill);
@@ -3573,11 +3613,12 @@ int orloj_set_score_chunk(orloj_ctx* ctx, int32_t steps) {
 
 int orloj_set_stream(orloj_ctx* ctx, void* hip_stream) {
     if (!ctx) return ORLOJ_E_INVALID;
-    if ((hipStream_t)hip_stream != ctx->stream && (ctx->work.p || ctx->drop.p || ctx->mix.p)) {
+    if ((hipStream_t)hip_stream != ctx->stream && (ctx->work.p || ctx->drop.p || ctx->mix_used)) {
         // calls still queued on the old stream may use the scratch
         hipError_t e = hipSetDevice(ctx->device);
         if (e == hipSuccess) e = hipStreamSynchronize(ctx->stream);
         if (e != hipSuccess) return hip_fail(ctx, e, "hipStreamSynchronize");
+        ctx->mix_used = false;
     }
     ctx->stream = (hipStream_t)hip_stream;
     return ORLOJ_OK;
@@ -4049,27 +4090,20 @@ int orloj_build_model_laws(orloj_ctx* ctx, const orloj_grid* grid, const float* 
     hipError_t e = hipSetDevice(ctx->device);
     if (e != hipSuccess) return hip_fail(ctx, e, "hipSetDevice");
     a.pm = nullptr;
-    const size_t pm_bytes = (size_t)nblk * (size_t)grid->n_bins * sizeof(double);
-    bool split = a.C >= 8 && nblk <= (ctx->n_cu > 0 ? ctx->n_cu : 256) && nblk * a.C <= 0x7fffffff;
-    // no scratch in a captured launch, which a later, larger call would free
-    if (split && !capturing(ctx)) {
-        rc = ensure_block(ctx, &ctx->mix, pm_bytes);
-        if (rc && rc != ORLOJ_E_NOMEM) return rc;
-        split = rc == ORLOJ_OK;  // no memory left: laws_kernel does without
-    } else {
-        split = false;
-    }
-    if (split) {
+    a.vshift = 0;
+    const int vpt = chunk_per_lane(grid->n_bins);
+    if (a.C >= 8 && nblk <= law_split_pairs(ctx) && nblk * a.C <= 0x7fffffff && ctx->mix.p && !capturing(ctx)) {
         a.pm = (double*)ctx->mix.p;
+        ctx->mix_used = true;
+        while ((1 << a.vshift) < vpt) ++a.vshift;
         const bool vec = a.K % 4 == 0 && ((uintptr_t)a.tab & 15) == 0;
         const int per = vec ? 4 : 1;
         const int mix_threads = std::min(kMixThreads, (a.K + 64 * per - 1) / (64 * per) * 64);
-        if (vec) hipLaunchKernelGGL(laws_mix_kernel<true>, dim3((unsigned)nblk), dim3(mix_threads), 0, ctx->stream, a);
-        else hipLaunchKernelGGL(laws_mix_kernel<false>, dim3((unsigned)nblk), dim3(mix_threads), 0, ctx->stream, a);
-        e = hipGetLastError();
+        e = vec ? launch_laws_mix<true>(a, (unsigned)nblk, mix_threads, ctx->stream)
+                : launch_laws_mix<false>(a, (unsigned)nblk, mix_threads, ctx->stream);
         if (e != hipSuccess) return hip_fail(ctx, e, "laws_mix_kernel launch");
         const unsigned rows = (unsigned)(nblk * a.C);
-        switch (chunk_per_lane(grid->n_bins)) {
+        switch (vpt) {
             case 1: e = launch_laws_rows<1>(a, rows, ctx->stream); break;
             case 2: e = launch_laws_rows<2>(a, rows, ctx->stream); break;
             case 4: e = launch_laws_rows<4>(a, rows, ctx->stream); break;
