@@ -1512,8 +1512,14 @@ __global__ __launch_bounds__(64) void emax_kernel(const ScoreArgs a) {
 //
 //   The tiles past every member's deadline only add their sums of 1 - G to
 //   E[L_B] (TurnedWave::e_tile): lanes hold the bins, the steps run in order
-//   and each step's lane sums are added up eight steps at a time from LDS.
-//   The waves take these tiles from a shared counter.
+//   and each step's lane sums are added up a few steps at a time from LDS.
+//   The waves take these tiles from a shared counter.  Rows of 4096 bins and
+//   short queues have most of their bins here, and what bounds them is the
+//   vector memory unit: loads of 64 consecutive floats a wave (256 bytes)
+//   instead of every other one, and no register copies that wait for loads in
+//   flight, took score + selection of one model of 4096 bins with prefixes to
+//   64 from 51 to 36 us on rows in no cache, where score_kernel in step chunks
+//   took 43; with tiles of 512 bins as well, prefixes to 4 took 22 -> 15 (19).
 //
 // What bounds it: latency.  A member's evaluation is ~300 cycles and a block
 // of bins ~2500 on a wave that has its SIMD nearly to itself, which is why
@@ -1531,7 +1537,9 @@ __global__ __launch_bounds__(64) void emax_kernel(const ScoreArgs a) {
 // the other models of the launch nor which wave takes which tile.
 // ---------------------------------------------------------------------------
 constexpr int kTurnWaves = 8;                   // waves of a workgroup
-constexpr int kETile = 128;                     // bins of an E tile: two per lane
+constexpr int kETile = 128;                     // bins of a narrow E tile: two per lane
+constexpr int kWide = 4;                        // narrow tiles in a wide one
+constexpr int kWideFrom = 8 * kETile;           // bins past the members from which tiles are wide
 constexpr int kPanel = 256;                     // bins of one affine E sum
 // most affine E sums turned_esum_kernel writes: doubles that the fixed scratch
 // array holds, so that the allocation-free call takes the same kernels
@@ -1696,16 +1704,31 @@ struct TurnedWave {
         }
     }
 
-    // Sum of G over the valid bins of the kETile bins from tile0 on, prefix
+    // Sum of G over the valid bins of the NS kETile bins from tile0 on, prefix
     // length 64 blk + lane + 1.  Rows whose support misses the tile are not
     // read: past a row's last bin with mass 1 - F is exactly 0 (G is
     // unchanged), before its first exactly 1 (G becomes 0), so the sums are
-    // the same bits with and without the support.
+    // the same bits with and without the support.  The rows of the next GS
+    // steps are on their way while GS are worked on, in two sets of registers
+    // that take turns: a copy from one to the other would wait for the loads.
+    template <int NS>
     __device__ __forceinline__ double e_tile(int tile0) {
-        const int tend = min(tile0 + kETile, K);
-        const int b0 = tile0 + 2 * lane;
-        const unsigned o0 = 4u * (unsigned)min(b0, K - 1), o1 = 4u * (unsigned)min(b0 + 1, K - 1);
-        double G0 = b0 < K ? 1.0 : 0.0, G1 = b0 + 1 < K ? 1.0 : 0.0;
+        constexpr int GS = NS == 1 ? 8 : 4;                // steps of a group
+        const int tend = min(tile0 + NS * kETile, K);
+        unsigned off[2 * NS];
+        double G[2 * NS];
+#pragma unroll
+        for (int j = 0; j < 2 * NS; ++j) {
+            const int b = tile0 + 64 * j + lane;           // a load takes 256 bytes of a row
+            off[j] = 4u * (unsigned)min(b, K - 1);
+            G[j] = b < K ? 1.0 : 0.0;
+        }
+        auto lane_sum = [&] {
+            double s = G[0] + G[1];
+#pragma unroll
+            for (int j = 2; j < 2 * NS; j += 2) s += G[j] + G[j + 1];
+            return s;
+        };
         int nstop = 0x7fffffff;                            // first member wholly past the tile
 #pragma unroll
         for (int r = 0; r < R; ++r) {
@@ -1729,43 +1752,40 @@ struct TurnedWave {
                 wave_lds_fence();
                 const unsigned lv = cnt > 0 ? lds_at<unsigned>(area + l.list + 4 * min(lane, cnt - 1)) : 0u;
                 const bool rows = r == blk;
-                // the rows of the 16 steps after the eight worked on are on
-                // their way
-                float t[3][8][2];
-                auto load = [&](float (&v)[8][2], int g) {
+                float ta[GS][2 * NS], tb[GS][2 * NS];
+                auto load = [&](float (&v)[GS][2 * NS], int g) {
 #pragma unroll
-                    for (int u = 0; u < 8; ++u) {
-                        const unsigned c = (unsigned)__builtin_amdgcn_readlane((int)lv, (g + u) & 63);
-                        v[u][0] = row_at(c + o0);
-                        v[u][1] = row_at(c + o1);
+                    for (int u = 0; u < GS; ++u) {
+                        const unsigned c = (unsigned)__builtin_amdgcn_readlane((int)lv, min(g + u, 63));
+#pragma unroll
+                        for (int j = 0; j < 2 * NS; ++j) v[u][j] = row_at(c + off[j]);
                     }
                 };
-                load(t[0], 0);
-                load(t[1], 8);
-#pragma unroll 1
-                for (int g = 0; g < cnt; g += 8) {
-                    load(t[2], g + 16);
+                auto steps = [&](const float (&v)[GS][2 * NS], int g) {
 #pragma unroll
-                    for (int u = 0; u < 8; ++u) {
+                    for (int u = 0; u < GS; ++u) {
                         if (g + u < cnt) {
-                            G0 = fma(-G0, (double)t[0][u][0], G0);
-                            G1 = fma(-G1, (double)t[0][u][1], G1);
+#pragma unroll
+                            for (int j = 0; j < 2 * NS; ++j) G[j] = fma(-G[j], (double)v[u][j], G[j]);
                         }
-                        if (rows) lds_at<double>(area + u * kERow + 8 * lane) = G0 + G1;
+                        if (rows) lds_at<double>(area + u * kERow + 8 * lane) = lane_sum();
                     }
-                    if (rows) add_rows(g);
-#pragma unroll
-                    for (int u = 0; u < 8; ++u)
-#pragma unroll
-                        for (int j = 0; j < 2; ++j) {
-                            t[0][u][j] = t[1][u][j];
-                            t[1][u][j] = t[2][u][j];
-                        }
+                    if (rows) add_rows<GS>(g);
+                };
+                load(ta, 0);
+#pragma unroll 1
+                for (int g = 0; g < cnt; g += 2 * GS) {
+                    load(tb, g + GS);
+                    steps(ta, g);
+                    if (g + GS < cnt) {
+                        load(ta, g + 2 * GS);
+                        steps(tb, g + GS);
+                    }
                 }
                 if (r + 1 == blk) {
                     // G of the block before: its sum, for the block's first prefixes
-                    lds_at<double>(area + 8 * lane) = G0 + G1;
-                    add_rows(0);
+                    lds_at<double>(area + 8 * lane) = lane_sum();
+                    add_rows<GS>(0);
                     before = lds_at<double>(area + l.tot);
                 }
                 if (rows) {
@@ -1779,20 +1799,23 @@ struct TurnedWave {
         return sum;
     }
 
-    // the sums over the lanes of eight rows, to the totals from t0 on
+    // the sums over the lanes of GS rows, to the totals from t0 on
+    template <int GS>
     __device__ __forceinline__ void add_rows(int t0) {
+        constexpr int L = 64 / GS;                         // lanes a row
         wave_lds_fence();
-        const int row = lane >> 3, oct = lane & 7;         // eight lanes a row
+        const int row = lane / L, at = lane % L;
         double s = 0.0;
 #pragma unroll
-        for (int j = 0; j < 4; ++j) {
-            const double2 v = lds_at<double2>(area + row * kERow + 16 * (8 * j + oct));
+        for (int j = 0; j < 32 / L; ++j) {
+            const double2 v = lds_at<double2>(area + row * kERow + 16 * (L * j + at));
             s = j == 0 ? v.x + v.y : s + (v.x + v.y);
         }
         s += dpp64<0xb1>(s);       // quad_perm 1 0 3 2
         s += dpp64<0x4e>(s);       // quad_perm 2 3 0 1
         s += dpp64<0x141>(s);      // row_half_mirror
-        if (oct == 0) lds_at<double>(area + l.tot + 8 * (t0 + row)) = s;
+        if (L == 16) s += dpp64<0x140>(s);                 // row_mirror
+        if (at == 0) lds_at<double>(area + l.tot + 8 * (t0 + row)) = s;
         wave_lds_fence();
     }
 };
@@ -1813,6 +1836,10 @@ __device__ __forceinline__ void turned_block(const TurnedArgs& a) {
     constexpr int W = kTurnWaves;
     const int K = a.K;
     constexpr TurnedLds l = turned_lds(R, W);
+    // E tiles handed out.  The barrier comes before the loads: it would wait
+    // for them.
+    if (tid == 0) lds_at<int>(l.ctrl) = 0;
+    __syncthreads();
 
     const unsigned per_bs = (unsigned)a.Mg * (unsigned)a.nblk;
     const int bi = a.nbs - 1 - (int)(blockIdx.x / per_bs);
@@ -1864,9 +1891,6 @@ __device__ __forceinline__ void turned_block(const TurnedArgs& a) {
     const double nowq = a.now[q];
     const double b = a.b, bw = b * w;
 
-    if (tid == 0) lds_at<int>(l.ctrl) = 0;                 // E tiles handed out
-    __syncthreads();
-
     // ---- deadline bins: -1 dead, K beyond the grid
     double th[R], left[R];                                 // position in the bin; time past its left edge
     int kk[R];
@@ -1912,8 +1936,41 @@ __device__ __forceinline__ void turned_block(const TurnedArgs& a) {
     }
     kmax = __builtin_amdgcn_readfirstlane(wave_max_i32(kmax));
 
+    // lane (row, i) of a segment: prefix length nidx + 1, part `part` of a block
+    const int S = nb <= 16 ? 4 : nb <= 32 ? 2 : 1, RG = 4 / S;
+    const int row = lane >> 4, ri = lane & 15, part = row % S, grp = row / S;
+    const int nrel = 16 * grp + ri, nidx = nrel < nb ? 64 * blk + nrel : -1;
+    const int row0 = 16 * grp * S + ri;                    // the lane of part 0 of this prefix length
+    // the member region: blocks of 16 S bins up to the last deadline, the
+    // same number of them for each segment
+    const int nblocks = kmax / (16 * S) + 1, per = (nblocks + W - 1) / W;
+    const int Ls = per * 16 * S, kend0 = nblocks * 16 * S, lseg = (nblocks - 1) / per;
+    const double omd = one_minus_exp(bw), d = 1.0 - omd;
+    double accP = 0.0, accN = 0.0, accC = 0.0, es = 0.0;   // this wave's segment: sums of P, N, C and G
+    double Y = 0.0, gpc = 0.0;                             // discounted prefix and G before the block
+
+    // The rows of a block of bins are loaded 16 members at a time per DPP row:
+    // passes over the members before this block of prefix lengths, then the
+    // block's own.  An item is one pass; the next item's rows are on their way
+    // while one is worked on.
+    const int k0 = wv * Ls, kend = min(k0 + Ls, kend0);
+    const int passes = blk * S + 1;
+    float tv[16], tn[16];
+    auto issue = [&](int base, int p) {
+        unsigned c = t.co[0];
+#pragma unroll
+        for (int r = 1; r < R; ++r) c = p / S == r ? t.co[r] : c;
+        if (S > 1) c = (unsigned)__shfl((int)c, 16 * ((p % S) * RG + grp) + ri, 64);
+        // (the last entry of a row is 0: bins past the grid hold G = 1)
+        const unsigned o = 4u * (unsigned)min(base + 16 * part + ri, K - 1);
+        unroll<16>([&](auto j) { tn[decltype(j)::value] = t.row_at(row_bcast<decltype(j)::value>(c) + o); });
+    };
+    // the block before the segment only gives G at its last bin
+    int base = k0 - (wv > 0 ? 16 * S : 0), pass = 0;
+    if (wv <= lseg) issue(base, 0);
+
     // this batch size's block of candidates and member slots starts after
-    // those of the batch sizes before it
+    // those of the batch sizes before it (their sizes are a memory round trip)
     {
         int dc = 0, dp = 0;                                // (caps are at most ORLOJ_MAX_PREFIX)
         for (int j0 = 0; j0 < bi; j0 += 64) {
@@ -1927,44 +1984,11 @@ __device__ __forceinline__ void turned_block(const TurnedArgs& a) {
         cand += wave_sum_i32(dc);
         prob += wave_sum_i32(dp);
     }
-
-    // lane (row, i) of a segment: prefix length nidx + 1, part `part` of a block
-    const int S = nb <= 16 ? 4 : nb <= 32 ? 2 : 1, RG = 4 / S;
-    const int row = lane >> 4, ri = lane & 15, part = row % S, grp = row / S;
-    const int nrel = 16 * grp + ri, nidx = nrel < nb ? 64 * blk + nrel : -1;
-    const int row0 = 16 * grp * S + ri;                    // the lane of part 0 of this prefix length
     float* const Pn = a.P + prob + (int64_t)nidx * (nidx + 1) / 2;   // this prefix length's P (R > 1)
-    // the member region: blocks of 16 S bins up to the last deadline, the
-    // same number of them for each segment
-    const int nblocks = kmax / (16 * S) + 1, per = (nblocks + W - 1) / W;
-    const int Ls = per * 16 * S, kend0 = nblocks * 16 * S, lseg = (nblocks - 1) / per;
-    const double omd = one_minus_exp(bw), d = 1.0 - omd;
-    double accP = 0.0, accN = 0.0, accC = 0.0, es = 0.0;   // this wave's segment: sums of P, N, C and G
-    double Y = 0.0, gpc = 0.0;                             // discounted prefix and G before the block
 
     // ---- member segments, one per wave
     if (wv <= lseg) {
         __builtin_amdgcn_s_setprio(3);                     // the others wait for these
-        const int k0 = wv * Ls, kend = min(k0 + Ls, kend0);
-        // The rows of a block of bins are loaded 16 members at a time per DPP
-        // row: passes over the members before this block of prefix lengths,
-        // then the block's own.  An item is one pass; the next item's rows
-        // are on their way while one is worked on.
-        const int passes = blk * S + 1;
-        float tv[16], tn[16];
-        auto issue = [&](int base, int p) {
-            unsigned c = t.co[0];
-#pragma unroll
-            for (int r = 1; r < R; ++r) c = p / S == r ? t.co[r] : c;
-            if (S > 1) c = (unsigned)__shfl((int)c, 16 * ((p % S) * RG + grp) + ri, 64);
-            // (the last entry of a row is 0: bins past the grid hold G = 1)
-            const unsigned o = 4u * (unsigned)min(base + 16 * part + ri, K - 1);
-            unroll<16>([&](auto j) { tn[decltype(j)::value] = t.row_at(row_bcast<decltype(j)::value>(c) + o); });
-        };
-        // the block before the segment only gives G at its last bin
-        int base = k0 - (wv > 0 ? 16 * S : 0), pass = 0;
-        issue(base, 0);
-
         int me = 0, mb = 0;                                // its members
 #pragma unroll
         for (int r = 0; r < R; ++r) {
@@ -2117,12 +2141,18 @@ __device__ __forceinline__ void turned_block(const TurnedArgs& a) {
     // length 64 blk + n + 1
     double eacc = 0.0;
     if constexpr (!AFF) {
+        // Wide where there are many: a tile is a chain of latencies whatever its
+        // width.  The width does not depend on the launch, so neither does the
+        // rounding of the sums.
+        const bool wide = K - kend0 > kWideFrom;
+        const int width = wide ? kWide * kETile : kETile;
         for (;;) {
             int T = 0;
             if (lane == 0) T = atomicAdd(&lds_at<int>(l.ctrl), 1);
-            const int tile0 = kend0 + kETile * __builtin_amdgcn_readfirstlane(T);
+            const int tile0 = kend0 + width * __builtin_amdgcn_readfirstlane(T);
             if (tile0 >= K) break;
-            eacc += round_e((double)(min(tile0 + kETile, K) - tile0) - t.e_tile(tile0));
+            const double G = wide ? t.template e_tile<kWide>(tile0) : t.template e_tile<1>(tile0);
+            eacc += round_e((double)(min(tile0 + width, K) - tile0) - G);
         }
     }
 
@@ -2215,7 +2245,7 @@ __global__ __launch_bounds__(128) void turned_esum_kernel(const TurnedArgs) {
     static_assert(kPanel == 2 * kETile, "a tile per wave");
     const int tile0 = p * kPanel + wv * kETile;
     double e = 0.0;
-    if (tile0 < a.K) e = round_e((double)(min(tile0 + kETile, a.K) - tile0) - t.e_tile(tile0));
+    if (tile0 < a.K) e = round_e((double)(min(tile0 + kETile, a.K) - tile0) - t.template e_tile<1>(tile0));
     __syncthreads();
     lds_at<double>(512 * wv + 8 * lane) = e;
     __syncthreads();

@@ -4,7 +4,7 @@ and against each other.
 
 The sizes lie at turned_kernel's edges: prefixes of 16, 32 and 64 members (parts
 of a block), one, two and four blocks of 64 prefix lengths, blocks of 16, 32 and
-64 bins, tiles of 128 bins, rows shorter than a block, deadlines beyond the grid
+64 bins, tiles of 128 and 512 bins, rows shorter than a block, deadlines beyond the grid
 where the grid's end lies inside a block and on its edge, a single member.
 """
 import dataclasses
@@ -43,6 +43,15 @@ CASES = [
     dict(seed=112, queue_lens=[100, 0, 7], n_models=3, batch_sizes=(5, 90), n_bins=600, b_expo=0.2,
          tau_range=(-10.0, 900.0)),
     dict(seed=113, queue_lens=[30, 60], batch_sizes=(30, 60), n_bins=8192, n_classes=2, tau_range=(0.0, 12000.0)),
+    # every deadline in the first bin: 1024 bins past the members (narrow tiles), one more
+    # (wide tiles), a wide tile of one bin, of all its bins, members in two and four blocks
+    dict(seed=114, queue_lens=[16, 9], batch_sizes=(9, 16), n_bins=64 + 1024, tau_range=(-0.1, 0.4)),
+    dict(seed=115, queue_lens=[16, 9], batch_sizes=(9, 16), n_bins=64 + 1025, tau_range=(-0.1, 0.4)),
+    dict(seed=116, queue_lens=[40, 33], batch_sizes=(33, 40), n_bins=16 + 1536, tau_range=(-0.1, 0.4),
+         sparsity=0.95),
+    dict(seed=117, queue_lens=[70, 66], batch_sizes=(64, 70), n_bins=64 + 1537, tau_range=(-0.1, 0.4)),
+    dict(seed=118, n_models=1, queue_lens=[200], batch_sizes=(130, 200), n_bins=2600, n_classes=5,
+         tau_range=(-0.1, 0.4)),
 ]
 
 
