@@ -1521,22 +1521,26 @@ __global__ __launch_bounds__(64) void emax_kernel(const ScoreArgs a) {
 //   64 from 51 to 36 us on rows in no cache, where score_kernel in step chunks
 //   took 43; with tiles of 512 bins as well, prefixes to 4 took 22 -> 15 (19).
 //
-// What bounds it: latency.  A member's evaluation is ~300 cycles and a block
-// of bins ~2500 on a wave that has its SIMD nearly to itself, which is why
-// the segments cut the member region evenly.  Score + selection, us, against
-// score_kernel in step chunks, the way taken before: 1 model of 128 bins and
-// prefixes to 16 15.8 -> 14.7; 1024 bins, to 64 33.1 -> 19.5; 2048 bins, to
-// 128 146 -> 57; 5 models, 1501 bins, every prefix to 100 152 -> 39.
+// What bounds it: latency, which is why the segments cut the member region
+// evenly.  Its registers (188 to 234 a lane) leave two waves per SIMD, one
+// workgroup of eight waves or two of four on a compute unit: a launch of more
+// workgroups than compute units takes four (512 workgroups, prefixes to 32,
+// 256 bins 26.7 -> 18.3 us, 1024 bins 27.6 -> 24.3; 64 workgroups 17.3 / 17.1
+// and 17.6 / 20.1).  Capped at 128 registers, so that two workgroups of eight
+// fit, it spills and takes 22.4 and 30.9 us there.  Score + selection, us,
+// against score_kernel in step chunks, the way taken before: 1 model of 128
+// bins and prefixes to 16 15.8 -> 14.9; 1024 bins, to 64 33.2 -> 19.0; 2048
+// bins, to 128 144 -> 53; 5 models, 1501 bins, every prefix to 100 152 -> 36.
 //
 // G is an fp64 product.  Within a group of 16 members it is chained from 1,
 // then multiplied by the product of the groups before: a member whose 1 - F
 // is 0 leaves every bit of it unchanged, so exact ties between prefixes stay
 // ties.  The segments depend on the queue and the batch size alone, and E's
 // sums over a segment or tile are rounded to multiples of 2^-40 before they
-// are added (any order gives the same sum), so the results depend on neither
-// the other models of the launch nor which wave takes which tile.
+// are added (any order gives the same sum), so it does not matter which wave
+// takes which tile.  The number of waves sets the segments and with them the
+// last bits of E and the scores.
 // ---------------------------------------------------------------------------
-constexpr int kTurnWaves = 8;                   // waves of a workgroup
 constexpr int kETile = 128;                     // bins of a narrow E tile: two per lane
 constexpr int kWide = 4;                        // narrow tiles in a wide one
 constexpr int kWideFrom = 8 * kETile;           // bins past the members from which tiles are wide
@@ -1829,11 +1833,10 @@ struct alignas(16) Plan {
 };
 static_assert(sizeof(Plan) == 32, "plan size");
 
-template <int R, bool AFF>
+template <int R, bool AFF, int W>
 __device__ __forceinline__ void turned_block(const TurnedArgs& a) {
     const int tid = threadIdx.x, lane = tid & 63;
     const int wv = __builtin_amdgcn_readfirstlane(tid >> 6);
-    constexpr int W = kTurnWaves;
     const int K = a.K;
     constexpr TurnedLds l = turned_lds(R, W);
     // E tiles handed out.  The barrier comes before the loads: it would wait
@@ -2211,9 +2214,9 @@ __device__ __forceinline__ void turned_block(const TurnedArgs& a) {
     }
 }
 
-template <int R, bool AFF>
-__global__ __launch_bounds__(64 * kTurnWaves) void turned_kernel(const TurnedArgs) {
-    turned_block<R, AFF>(kernel_args<TurnedArgs>());
+template <int R, bool AFF, int W>
+__global__ __launch_bounds__(64 * W) void turned_kernel(const TurnedArgs) {
+    turned_block<R, AFF, W>(kernel_args<TurnedArgs>());
 }
 
 // The sums of 1 - G behind E[max] in the affine mode (see emax_kernel), for
@@ -3491,36 +3494,38 @@ hipError_t launch_emax(const ScoreArgs& a, hipStream_t st) {
     return hipGetLastError();
 }
 
-template <int R, bool AFF>
-hipError_t launch_turned_v(const TurnedArgs& a, hipStream_t st) {
+template <int R, bool AFF, int W>
+hipError_t launch_turned_w(const TurnedArgs& a, hipStream_t st) {
     if constexpr (AFF) {
         const unsigned g = (unsigned)a.Mg * (unsigned)a.np_e * (unsigned)a.nblk;
         hipLaunchKernelGGL((turned_esum_kernel<R>), dim3(g), dim3(128), turned_lds(R, 2).total, st, a);
         const hipError_t e = hipGetLastError();
         if (e != hipSuccess) return e;
     }
-    constexpr int lds = turned_lds(R, kTurnWaves).total;
+    constexpr int lds = turned_lds(R, W).total;
     static std::atomic<int> allowed{64 * 1024};   // per template instance; device-independent
     if (lds > allowed.load(std::memory_order_relaxed)) {
-        const hipError_t e = hipFuncSetAttribute((const void*)turned_kernel<R, AFF>,
+        const hipError_t e = hipFuncSetAttribute((const void*)turned_kernel<R, AFF, W>,
                                                  hipFuncAttributeMaxDynamicSharedMemorySize, lds);
         if (e != hipSuccess) return e;
         allowed.store(lds, std::memory_order_relaxed);
     }
     const unsigned g = (unsigned)a.Mg * (unsigned)a.nbs * (unsigned)a.nblk;
-    hipLaunchKernelGGL((turned_kernel<R, AFF>), dim3(g), dim3(64 * kTurnWaves), lds, st, a);
+    hipLaunchKernelGGL((turned_kernel<R, AFF, W>), dim3(g), dim3(64 * W), lds, st, a);
     return hipGetLastError();
 }
 
 template <int R>
-hipError_t launch_turned_r(const TurnedArgs& a, hipStream_t st) {
-    return a.c1 ? launch_turned_v<R, true>(a, st) : launch_turned_v<R, false>(a, st);
+hipError_t launch_turned_r(const TurnedArgs& a, int waves, hipStream_t st) {
+    if (waves == 8) return a.c1 ? launch_turned_w<R, true, 8>(a, st) : launch_turned_w<R, false, 8>(a, st);
+    return a.c1 ? launch_turned_w<R, true, 4>(a, st) : launch_turned_w<R, false, 4>(a, st);
 }
 
-hipError_t launch_turned(const TurnedArgs& a, hipStream_t st) {
+// `waves`: 8 or 4 per workgroup.
+hipError_t launch_turned(const TurnedArgs& a, int waves, hipStream_t st) {
     static_assert(ORLOJ_MAX_PREFIX <= 256, "four registers of members");
-    if (a.maxcap <= 64) return launch_turned_r<1>(a, st);
-    return a.maxcap <= 128 ? launch_turned_r<2>(a, st) : launch_turned_r<4>(a, st);
+    if (a.maxcap <= 64) return launch_turned_r<1>(a, waves, st);
+    return a.maxcap <= 128 ? launch_turned_r<2>(a, waves, st) : launch_turned_r<4>(a, waves, st);
 }
 
 template <int VPT>
@@ -3803,7 +3808,7 @@ int score_common(orloj_ctx* ctx, const orloj_grid* grid, const float* d_ccdf,
         return orloj_ctx_fail(ctx, ORLOJ_E_INVALID, "b_expo_per_ms must be finite and > 0");
     const int M = grid->n_models;
     if (M == 0) return ORLOJ_OK;
-    int64_t maxcap = 0, total = 0, active = 0;
+    int64_t maxcap = 0, total = 0, groups = 0;             // groups: workgroups of turned_kernel
     int n_act = 0;
     int act[kMaxActive];
     for (int q = 0; q < M; ++q) {
@@ -3815,7 +3820,7 @@ int score_common(orloj_ctx* ctx, const orloj_grid* grid, const float* d_ccdf,
             const int64_t c = ncap_of(N, grid->batch_sizes[bi], prefix_mode);
             if (c > maxcap) maxcap = c;
             total += c;
-            active += c > 0;
+            groups += (c + 63) / 64;
         }
     }
     if (maxcap > ORLOJ_MAX_PREFIX)
@@ -3837,18 +3842,34 @@ int score_common(orloj_ctx* ctx, const orloj_grid* grid, const float* d_ccdf,
     if (nblk > 0x7fffffff) return orloj_ctx_fail(ctx, ORLOJ_E_UNSUPPORTED, "too many (model, batch size) pairs");
 
     // Launches too small to fill the chip go to turned_kernel (its row offsets
-    // are 32-bit).  score_kernel takes about as long
-    // for one pair as for a full chip, turned_kernel's time grows with the
-    // pairs past one workgroup per compute unit, so the line lies where they
-    // meet: score + selection, us, score_kernel / turned_kernel, at
-    //   512 pairs:  20.1 / 21.7 (256 bins, prefixes to 16), 32.9 / 26.6
-    //     (1024 bins, to 32), 55 / 34 (1024, to 64), 44 / 43 (4096, to 12)
-    //   1024 pairs: 20.5 / 34 (256, 16), 35 / 45 (1024, 32), 59 / 58 (1024,
-    //     64), 177 / 126 (4096, 64), 187 / 205 (2048, 100).
-    const int simds = 4 * (ctx->n_cu > 0 ? ctx->n_cu : 256);
-    const bool longest = maxcap == 64 && grid->n_bins >= 1024;
+    // are 32-bit).  Its time grows with its workgroups, two of which run on a
+    // compute unit at once.  score_kernel's is a chain of as many steps as the
+    // longest prefix has members, in rows of several panels some of them for
+    // each, and grows little until the chip is full.  So the line lies at a
+    // number of workgroups proportional to the longest prefix.  Score +
+    // selection, us, score_kernel / turned_kernel, deadlines over most of the
+    // grid (the less favourable case: members in more of the bins):
+    //   256 bins: prefixes to 24, 640 workgroups 24.8 / 24.1, 768 25.2 / 25.5;
+    //     to 32, 1024 29.9 / 28.5, 1280 30.1 / 33.3; to 64, 2048 46.6 / 47.1
+    //   1024 bins: to 24, 640 29.4 / 29.7, 768 30.6 / 34.2; to 48, 1280 49.9 /
+    //     50.4; to 63, 1536 60.5 / 54.5, 2048 63.0 / 71.7; to 64, 1280 60.2 /
+    //     49.8, 1536 61.5 / 54.8; to 65, 1536 93.1 / 96.7
+    //   2048 bins: to 16, 768 38.1 / 37.7; to 48, 1536 86 / 76, 2048 88 / 100
+    //   4096 bins: to 8, 640 38.1 / 40.7; to 48, 2048 152 / 148
+    // One round of workgroups takes about as long whatever their number: there
+    // it is the faster one from about ten members on (1024 bins, 512
+    // workgroups: to 8 17.4 / 19.2, to 12 20.4 / 19.9, to 16 23.4 / 20.4; 384:
+    // the same within 5%).  Affine mode: score_kernel waits for a launch of
+    // emax_kernel's, so the line lies higher: 1024 bins, prefixes to 8, 512
+    // workgroups 39 / 23, 768 40 / 29 (24.0 / 25.0 with short deadlines); to
+    // 64, 2048 54.1 / 56.3.
+    const int64_t n_cu = ctx->n_cu > 0 ? ctx->n_cu : 256;
+    const int64_t one_round = groups <= 2 * n_cu ? std::min(groups, 5 * n_cu / 4) : groups;
+    const int64_t launched = nblk * ((maxcap + 63) / 64);   // with those that find nothing to do
     const int64_t np_t = (grid->n_bins + kPanel - 1) / kPanel;
-    const bool turned = active <= (longest ? simds : simds / 2) &&
+    const bool turned = (d_c1 ? groups <= 2 * n_cu + 24 * maxcap
+                              : one_round <= (20 + 11 * panels) * maxcap) &&
+                        launched <= 4 * groups + n_cu &&
                         (int64_t)grid->n_classes * grid->n_bins <= 0x3fffffff &&
                         (!d_c1 || (int64_t)M * np_t * maxcap <= kTurnedSums);
     // Affine mode: the sums of 1 - G, [M][panels][maxcap], floats of
@@ -3918,7 +3939,9 @@ int score_common(orloj_ctx* ctx, const orloj_grid* grid, const float* d_ccdf,
             a.esum = (double*)(void*)psum;
             a.np_e = (int)np_t;
         }
-        e = launch_turned(a, ctx->stream);
+        // eight waves use a compute unit up, so more workgroups than units have
+        // four each and two run on one
+        e = launch_turned(a, groups <= n_cu ? 8 : 4, ctx->stream);
         if (e != hipSuccess) return hip_fail(ctx, e, "turned_kernel launch");
         return ORLOJ_OK;
     }

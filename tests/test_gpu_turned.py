@@ -1,6 +1,6 @@
-"""turned_kernel (launches with (model, batch size) pairs on fewer than half the
-SIMDs) and score_kernel (larger ones) on the same models, against the oracle
-and against each other.
+"""turned_kernel (launches of few (model, batch size) pairs, with eight waves a
+workgroup and with four) and score_kernel (larger ones) on the same models, against
+the oracle and against each other.
 
 The sizes lie at turned_kernel's edges: prefixes of 16, 32 and 64 members (parts
 of a block), one, two and four blocks of 64 prefix lengths, blocks of 16, 32 and
@@ -78,16 +78,35 @@ def test_both_kernels_against_the_oracle(ctx, case, law):
     ora = (oracle.score_workload_affine(one, one.c0_ms, one.c1, prefix_mode=mode) if law == "affine"
            else oracle.score_workload(one, prefix_mode=mode))
     parity.compare(one, small, ora, mode=mode)
-    # the same models over and over, in one launch of more than 512 pairs
-    M, B = one.n_models, one.n_bs
-    reps = 520 // (B * sum(one.queue_len(q) > 0 for q in range(M))) + 1
+    # the same models over and over: in one launch of more workgroups than compute units
+    # (four waves each), and in one of more than turned_kernel takes
+    M = one.n_models
+    caps = [[one.queue_len(q) if mode else min(one.queue_len(q), int(s)) for s in one.batch_sizes]
+            for q in range(M)]
+    groups, longest = sum((c + 63) // 64 for cs in caps for c in cs), max(max(cs) for cs in caps)
+    for most in (N_CU, past_turned(law, one.n_bins, longest)):
+        check_large(ctx, one, mode, most // groups + 1, small, ora)
+
+
+N_CU = 256
+
+
+def past_turned(law, n_bins, longest):
+    """Workgroups that turned_kernel does not take more of, whatever else holds."""
+    if law == "affine":
+        return 2 * N_CU + 24 * longest
+    return max(2 * N_CU, (20 + 11 * -(-n_bins // 1024)) * longest)
+
+
+def check_large(ctx, one, mode, reps, small, ora):
+    M = one.n_models
     large = run(one.subset(list(range(M)) * reps), ctx, mode, True)
     n, npr = small["score"].size, small["finish_prob"].size
     for r in (0, reps - 1):
         part = {k: v[r * (npr if k == "finish_prob" else M if k.startswith("sel") else n):][:v.size // reps]
                 for k, v in large.items()}
         parity.compare(one, part, ora, mode=mode)
-        # between the kernels: G's products agree to 256 x 2^-53, so P to one
+        # between the kernels, or two splits of the bins: G's products agree to 256 x 2^-53, so P to one
         # fp32 rounding (2^-24 at most) and E to the sum of the members' 2^-45
         assert np.abs(part["finish_prob"] - small["finish_prob"]).max(initial=0.0) <= 2.0**-24
         assert np.allclose(part["expected_finish"], small["expected_finish"], rtol=1e-12, atol=1e-12)
