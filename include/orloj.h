@@ -73,16 +73,15 @@ typedef struct orloj_ctx orloj_ctx;
 
 /* Create a context on HIP device `hip_device` that enqueues on `hip_stream`
  * (a hipStream_t; NULL = the null stream).  Allocates a small device status
- * word and, if the device has it to spare, the scratch of
- * orloj_build_model_laws (64 KiB per compute unit).  Returns ORLOJ_OK and *out, or an error with *out = NULL. */
+ * word.  Returns ORLOJ_OK and *out, or an error with *out = NULL. */
 int orloj_create(orloj_ctx **out, int32_t hip_device, void *hip_stream);
 
 /* Free a context (waits for its stream first).  NULL is a no-op. */
 void orloj_destroy(orloj_ctx *ctx);
 
 /* Switch the stream later calls enqueue on.  If the context holds a
- * scratch block (orloj_score_candidates_affine, or orloj_iterate on long
- * queues) or formed model laws, work already enqueued on the previous stream is waited for
+ * scratch block (orloj_score_candidates_affine, orloj_iterate on long queues,
+ * or orloj_build_model_laws of few pairs), work already enqueued on the previous stream is waited for
  * first. */
 int orloj_set_stream(orloj_ctx *ctx, void *hip_stream);
 
@@ -304,10 +303,11 @@ int orloj_select_batch(orloj_ctx *ctx, const orloj_grid *grid, const orloj_queue
  * its shape (float32), d_model_el is [M][n_bs] float32.  Negative, infinite
  * or all-zero weights of a model are a data error (orloj_sync).
  * With at least 8 classes and no more (model, batch size) pairs than compute
- * units, F_mix^(s_b - 1) goes through a block that the context has held since
- * orloj_create; without memory for it then, and on a stream under capture, the
- * laws are formed without it.  Every output has the same bits either way.  The
- * call allocates nothing and does not wait.
+ * units, F_mix^(s_b - 1) goes through a block of 64 KiB per compute unit that
+ * the context's first such call allocates (also while other threads capture
+ * streams) and the context keeps; without memory for it, and on a stream under
+ * capture, the laws are formed without it.  Every output has the same bits
+ * either way.  The call never waits for the device.
  *
  * orloj_iterate: one iteration for every model in one launch.  For model q
  * at time now_q, with tau_r = D_r - now_q:

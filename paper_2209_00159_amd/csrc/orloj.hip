@@ -3589,7 +3589,6 @@ int orloj_create(orloj_ctx** out, int32_t hip_device, void* hip_stream) {
     ctx->d_err = nullptr;
     ctx->d_fill = nullptr;
     ctx->work = ctx->drop = ctx->mix = orloj_block{nullptr, 0};
-    ctx->mix_used = false;
     ctx->noalloc_scratch = nullptr;
     ctx->noalloc_err = hipSuccess;
     ctx->msg[0] = 0;
@@ -3610,15 +3609,6 @@ int orloj_create(orloj_ctx** out, int32_t hip_device, void* hip_stream) {
     // the allocation-free scorer's scratch on this device (its failure only
     // disables that entry point)
     if (e == hipSuccess) ctx->noalloc_scratch = scratch_address(hip_device, &ctx->noalloc_err);
-    if (e == hipSuccess) {
-        const size_t bytes = (size_t)law_split_pairs(ctx) * ORLOJ_MAX_BINS * sizeof(double);
-        if (hipMalloc(&ctx->mix.p, bytes) == hipSuccess) {
-            ctx->mix.bytes = bytes;
-        } else {
-            ctx->mix.p = nullptr;   // laws_kernel does without
-            (void)hipGetLastError();
-        }
-    }
     if (e != hipSuccess) {
         if (ctx->d_err) (void)hipFree(ctx->d_err);
         if (ctx->d_fill) (void)hipFree(ctx->d_fill);
@@ -3648,12 +3638,11 @@ int orloj_set_score_chunk(orloj_ctx* ctx, int32_t steps) {
 
 int orloj_set_stream(orloj_ctx* ctx, void* hip_stream) {
     if (!ctx) return ORLOJ_E_INVALID;
-    if ((hipStream_t)hip_stream != ctx->stream && (ctx->work.p || ctx->drop.p || ctx->mix_used)) {
+    if ((hipStream_t)hip_stream != ctx->stream && (ctx->work.p || ctx->drop.p || ctx->mix.p)) {
         // calls still queued on the old stream may use the scratch
         hipError_t e = hipSetDevice(ctx->device);
         if (e == hipSuccess) e = hipStreamSynchronize(ctx->stream);
         if (e != hipSuccess) return hip_fail(ctx, e, "hipStreamSynchronize");
-        ctx->mix_used = false;
     }
     ctx->stream = (hipStream_t)hip_stream;
     return ORLOJ_OK;
@@ -3774,6 +3763,28 @@ int ensure_block(orloj_ctx* ctx, orloj_block* blk, size_t bytes) {
     }
     blk->bytes = bytes;
     return ORLOJ_OK;
+}
+
+// The laws' scratch, allocated at its first use; false: no memory for it.
+// The thread's capture mode is relaxed meanwhile: other threads may be
+// capturing streams of their own, which an allocation would end otherwise.
+bool have_mix(orloj_ctx* ctx) {
+    if (ctx->mix.p) return true;
+    const size_t bytes = (size_t)law_split_pairs(ctx) * ORLOJ_MAX_BINS * sizeof(double);
+    hipStreamCaptureMode mode = hipStreamCaptureModeRelaxed;
+    if (hipThreadExchangeStreamCaptureMode(&mode) != hipSuccess) {
+        (void)hipGetLastError();
+        return false;
+    }
+    const hipError_t e = hipMalloc(&ctx->mix.p, bytes);
+    (void)hipThreadExchangeStreamCaptureMode(&mode);
+    if (e == hipSuccess) {
+        ctx->mix.bytes = bytes;
+        return true;
+    }
+    ctx->mix.p = nullptr;
+    (void)hipGetLastError();
+    return false;
 }
 
 // Whether the context's stream is being captured (or cannot say).
@@ -4145,9 +4156,8 @@ int orloj_build_model_laws(orloj_ctx* ctx, const orloj_grid* grid, const float* 
     a.pm = nullptr;
     a.vshift = 0;
     const int vpt = chunk_per_lane(grid->n_bins);
-    if (a.C >= 8 && nblk <= law_split_pairs(ctx) && nblk * a.C <= 0x7fffffff && ctx->mix.p && !capturing(ctx)) {
+    if (a.C >= 8 && nblk <= law_split_pairs(ctx) && nblk * a.C <= 0x7fffffff && !capturing(ctx) && have_mix(ctx)) {
         a.pm = (double*)ctx->mix.p;
-        ctx->mix_used = true;
         while ((1 << a.vshift) < vpt) ++a.vshift;
         const bool vec = a.K % 4 == 0 && ((uintptr_t)a.tab & 15) == 0;
         const int per = vec ? 4 : 1;

@@ -1,6 +1,8 @@
 """The context's scratch blocks under HIP graph capture: a captured call does not
 lose its scratch to later calls of other kinds, and finds it whichever queues were
 filled in the calls before."""
+import threading
+
 import numpy as np
 import pytest
 import torch
@@ -107,17 +109,40 @@ def test_affine_bits_do_not_depend_on_the_scratch(warm):
             assert np.array_equal(v.view(np.uint8), got[k].view(np.uint8)), k
 
 
-def test_model_laws_allocate_nothing():
-    """64 pairs of 8192 bins: the powers of the class mix would be 4 MB."""
-    ctx = O.Context()
-    it = O.Iterator(W.random_case(13, n_models=1, n_classes=8, n_bins=8192, queue_lens=[0],
-                                  batch_sizes=tuple(range(1, 65))), ctx)
-    ctx.build_cdfs(it.counts, it.ccdf, it.support)
+def test_first_model_laws_while_another_thread_captures():
+    """The scratch of few pairs' laws is allocated by the first call that needs it, which
+    must not end the capture of another thread's stream nor fail because of it."""
+    ctx, ref = O.Context(stream=torch.cuda.Stream()), O.Context()
+    wl = W.random_case(13, n_models=1, n_classes=8, n_bins=8192, queue_lens=[0],
+                       batch_sizes=tuple(range(1, 65)))
+    it, want = O.Iterator(wl, ctx), O.Iterator(wl, ref)
+    x = torch.zeros(64, device="cuda")
+    want.build()
+    ref.sync()
+    failed = []
+
+    def laws():
+        try:
+            it.build()
+        except Exception as e:                 # (a thread's exception would be lost)
+            failed.append(e)
+
+    torch.cuda.synchronize()
+    g = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(g, stream=torch.cuda.Stream(), capture_error_mode="global"):
+        x += 1.0
+        t = threading.Thread(target=laws)
+        t.start()
+        t.join()
+        x += 1.0
+    assert not failed, failed
     ctx.sync()
-    free = torch.cuda.mem_get_info()[0]
-    it.build()
-    ctx.sync()
-    assert torch.cuda.mem_get_info()[0] == free
+    for a, b in ((it.law, want.law), (it.disc, want.disc), (it.model_el, want.model_el)):
+        assert torch.equal(a, b)
+    for n in (1, 2):
+        g.replay()
+        torch.cuda.synchronize()
+        assert float(x.min()) == float(x.max()) == 2.0 * n
 
 
 def test_captured_model_laws_use_no_scratch():
