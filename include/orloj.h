@@ -302,8 +302,8 @@ int orloj_select_batch(orloj_ctx *ctx, const orloj_grid *grid, const orloj_queue
  * d_ccdf is orloj_build_cdfs' [M][n_bs][C][K] table; d_law and d_disc have
  * its shape (float32), d_model_el is [M][n_bs] float32.  Negative, infinite
  * or all-zero weights of a model are a data error (orloj_sync).
- * With at least 8 classes and no more (model, batch size) pairs than compute
- * units, F_mix^(s_b - 1) goes through a block of 64 KiB per compute unit that
+ * With several classes and few (model, batch size) pairs (no more than compute
+ * units), F_mix^(s_b - 1) goes through a block of 8 KiB per compute unit that
  * the context's first such call allocates (also while other threads capture
  * streams) and the context keeps; without memory for it, and on a stream under
  * capture, the laws are formed without it.  Every output has the same bits

@@ -2553,7 +2553,7 @@ __device__ __forceinline__ void store_row(float* __restrict__ o, const float (&v
     store_chunk<VPT>(o, v, base, K);
 }
 
-template <int VPT>
+template <int VPT, bool AHEAD>
 __global__ __launch_bounds__(kThreads) void laws_kernel(const LawArgs a) {
     __shared__ float s_wave[2][kWaves];   // of a class, by its parity
     __shared__ __align__(16) float s_turn[kWaves][kTurnedRow<VPT> ? 64 * kTurnedRow<VPT> : 4];
@@ -2616,15 +2616,16 @@ __global__ __launch_bounds__(kThreads) void laws_kernel(const LawArgs a) {
     const float w31 = exp2_hw(log2d * (float)(VPT * (lane >= 32 ? lane - 31 : 0)));
     const float d_wave = exp2_hw(log2d * (float)(64 * VPT));
 
-    float t[VPT];   // the next class's row, loaded while a class is worked on
-    load_row_chunk<VPT>(t, a.tab + row0 * (size_t)K, base, K);
+    float t[VPT];   // AHEAD: the next class's row, loaded while a class is worked on
+    if (AHEAD) load_row_chunk<VPT>(t, a.tab + row0 * (size_t)K, base, K);
     for (int c = 0; c < C; ++c) {
         const size_t r = (row0 + (size_t)c) * (size_t)K;
         double g[VPT];
         double z = 0.0;
+        if (!AHEAD) load_row_chunk<VPT>(t, a.tab + r, base, K);
 #pragma unroll
         for (int j = 0; j < VPT; ++j) g[j] = (1.0 - (double)t[j]) * pm[j];
-        if (c + 1 < C) load_row_chunk<VPT>(t, a.tab + r + K, base, K);
+        if (AHEAD && c + 1 < C) load_row_chunk<VPT>(t, a.tab + r + K, base, K);
 #pragma unroll
         for (int j = 0; j < VPT; ++j) {
             z = fma(z, d, g[j]);
@@ -2653,16 +2654,29 @@ __global__ __launch_bounds__(kThreads) void laws_kernel(const LawArgs a) {
     }
 }
 
+// Short rows of few pairs load a class's row in its turn: the wait for one
+// loaded ahead comes after the stores of the class before and costs more than
+// it hides (64 pairs x 16 classes x 64 bins 18.0 us with the row ahead, 17.2
+// without; 256 x 16 x 1000 33.9 against 36.4, 2048 x 16 x 1000 158 against 165).
+template <int VPT>
+void launch_laws(const LawArgs& a, unsigned pairs, hipStream_t st) {
+    if constexpr (VPT <= 4) {
+        if (pairs <= (VPT < 4 ? 512u : 128u)) {
+            hipLaunchKernelGGL((laws_kernel<VPT, false>), dim3(pairs), dim3(kThreads), 0, st, a);
+            return;
+        }
+    }
+    hipLaunchKernelGGL((laws_kernel<VPT, true>), dim3(pairs), dim3(kThreads), 0, st, a);
+}
+
 // ---------------------------------------------------------------------------
 // laws_mix_kernel and laws_row_kernel: laws_kernel's outputs when the pairs
-// are no more than the compute units.  laws_kernel walks a pair's classes one
-// after another in one workgroup; here one workgroup per pair forms the class
-// mix and its power per bin (to scratch) and the model-wide E[L], and then
-// every row has a workgroup of its own.  Table and laws, us: 1 model x 64
-// batch sizes x 32 classes x 1024 bins 44 -> 24, 2 x 16 x 32 x 4096 105 -> 51,
-// 3 x 48 x 21 x 1501 101 -> 69, 8 x 32 x 16 x 1000 34.5 -> 31.  From 512
-// pairs on laws_kernel is faster (98 against 128 at 16 x 32 x 8 x 4096), and
-// so it is at a handful of classes (12.6 against 14.5 at 7).
+// are few (law_split).  laws_kernel walks a pair's classes one after another
+// in one workgroup; here one workgroup per pair forms the class mix and its
+// power per bin (to scratch) and the model-wide E[L], and then every row has
+// a workgroup of its own.  Table and laws, us: 1 model x 64 batch sizes x 32
+// classes x 1024 bins 44 -> 24, 2 x 16 x 32 x 4096 106 -> 52, 3 x 48 x 21 x
+// 1501 101 -> 70, 8 x 32 x 16 x 1000 35 -> 32.
 // ---------------------------------------------------------------------------
 constexpr int kMixThreads = 1024;
 
@@ -3408,9 +3422,21 @@ int chunk_per_lane(int K) {
     return c;
 }
 
-// Most (model, batch size) pairs whose laws are formed by laws_mix_kernel and
-// laws_row_kernel.
-int64_t law_split_pairs(const orloj_ctx* ctx) { return ctx->n_cu > 0 ? ctx->n_cu : 256; }
+// Whether the laws are formed by laws_mix_kernel and laws_row_kernel: pairs up
+// to the compute units, as many bins in all as keep the powers' way through
+// memory short, and classes enough to pay for a second launch.  Time against
+// laws_kernel's, on 256 compute units:
+//   16 classes, 256 bins: 64 pairs 0.77, 256 0.94; 1024 bins: 256 0.97; 2048
+//     bins: 128 0.83, 192 1.02; 4096 bins: 64 0.80, 128 1.14
+//   8 classes: 256 bins 1.02 to 1.12; 512 bins: 64 0.97, 256 1.02; 1024 bins:
+//     128 0.93, 256 1.08; 2048 bins: 64 0.83, 128 0.98; 4096 bins: 16 0.71,
+//     64 0.94
+int64_t law_split_bins(const orloj_ctx* ctx) { return 1024 * (int64_t)(ctx->n_cu > 0 ? ctx->n_cu : 256); }
+
+bool law_split(const orloj_ctx* ctx, int64_t pairs, int C, int K) {
+    const int64_t most = law_split_bins(ctx);
+    return C >= (K >= 512 ? 8 : 16) && 1024 * pairs <= most && pairs * K <= (C >= 16 ? most : most / 2);
+}
 
 
 template <int CPL, bool EXACT, int CR, bool AFF>
@@ -3770,7 +3796,7 @@ int ensure_block(orloj_ctx* ctx, orloj_block* blk, size_t bytes) {
 // capturing streams of their own, which an allocation would end otherwise.
 bool have_mix(orloj_ctx* ctx) {
     if (ctx->mix.p) return true;
-    const size_t bytes = (size_t)law_split_pairs(ctx) * ORLOJ_MAX_BINS * sizeof(double);
+    const size_t bytes = (size_t)law_split_bins(ctx) * sizeof(double);
     hipStreamCaptureMode mode = hipStreamCaptureModeRelaxed;
     if (hipThreadExchangeStreamCaptureMode(&mode) != hipSuccess) {
         (void)hipGetLastError();
@@ -4156,7 +4182,7 @@ int orloj_build_model_laws(orloj_ctx* ctx, const orloj_grid* grid, const float* 
     a.pm = nullptr;
     a.vshift = 0;
     const int vpt = chunk_per_lane(grid->n_bins);
-    if (a.C >= 8 && nblk <= law_split_pairs(ctx) && nblk * a.C <= 0x7fffffff && !capturing(ctx) && have_mix(ctx)) {
+    if (law_split(ctx, nblk, a.C, a.K) && nblk * a.C <= 0x7fffffff && !capturing(ctx) && have_mix(ctx)) {
         a.pm = (double*)ctx->mix.p;
         while ((1 << a.vshift) < vpt) ++a.vshift;
         const bool vec = a.K % 4 == 0 && ((uintptr_t)a.tab & 15) == 0;
@@ -4178,13 +4204,13 @@ int orloj_build_model_laws(orloj_ctx* ctx, const orloj_grid* grid, const float* 
         return ORLOJ_OK;
     }
     const unsigned g = (unsigned)nblk;
-    switch (chunk_per_lane(grid->n_bins)) {
-        case 1: hipLaunchKernelGGL(laws_kernel<1>, dim3(g), dim3(kThreads), 0, ctx->stream, a); break;
-        case 2: hipLaunchKernelGGL(laws_kernel<2>, dim3(g), dim3(kThreads), 0, ctx->stream, a); break;
-        case 4: hipLaunchKernelGGL(laws_kernel<4>, dim3(g), dim3(kThreads), 0, ctx->stream, a); break;
-        case 8: hipLaunchKernelGGL(laws_kernel<8>, dim3(g), dim3(kThreads), 0, ctx->stream, a); break;
-        case 16: hipLaunchKernelGGL(laws_kernel<16>, dim3(g), dim3(kThreads), 0, ctx->stream, a); break;
-        default: hipLaunchKernelGGL(laws_kernel<32>, dim3(g), dim3(kThreads), 0, ctx->stream, a); break;
+    switch (vpt) {
+        case 1: launch_laws<1>(a, g, ctx->stream); break;
+        case 2: launch_laws<2>(a, g, ctx->stream); break;
+        case 4: launch_laws<4>(a, g, ctx->stream); break;
+        case 8: launch_laws<8>(a, g, ctx->stream); break;
+        case 16: launch_laws<16>(a, g, ctx->stream); break;
+        default: launch_laws<32>(a, g, ctx->stream); break;
     }
     e = hipGetLastError();
     if (e != hipSuccess) return hip_fail(ctx, e, "laws_kernel launch");

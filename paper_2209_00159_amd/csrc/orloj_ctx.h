@@ -26,8 +26,8 @@ struct orloj_ctx {
     // still name, so each use has a block that only its own larger calls grow.
     orloj_block work;  // the affine scorer's sums (emax_kernel, turned_esum_kernel)
     orloj_block drop;  // iterate_kernel's split drop phase
-    // laws_mix_kernel's powers, for as many pairs of the longest rows as it takes,
-    // so that it is allocated once and never grown.  Never used under capture: a
+    // laws_mix_kernel's powers, for as many bins as it takes, so that it is
+    // allocated once and never grown.  Never used under capture: a
     // graph may be replayed beside this context's own laws.
     orloj_block mix;
     float* noalloc_scratch;   // this device's fixed scratch array (NULL: unavailable)

@@ -25,7 +25,7 @@ def laws(wl, ctx, weights):
 
 
 @pytest.mark.parametrize("n_bins", [1, 3, 4, 255, 256, 257, 1000, 1023, 2048, 4097, 8192])
-@pytest.mark.parametrize("n_classes", [8, 33])
+@pytest.mark.parametrize("n_classes", [8, 16, 33])   # (8: rows of 512 bins or more)
 def test_few_pairs_give_the_bits_of_many(ctx, n_bins, n_classes):
     print("laws", n_bins, n_classes, flush=True)
     one = W.random_case(n_bins, n_models=1, n_classes=n_classes, n_bins=n_bins, queue_lens=[0],

@@ -114,7 +114,7 @@ def test_first_model_laws_while_another_thread_captures():
     must not end the capture of another thread's stream nor fail because of it."""
     ctx, ref = O.Context(stream=torch.cuda.Stream()), O.Context()
     wl = W.random_case(13, n_models=1, n_classes=8, n_bins=8192, queue_lens=[0],
-                       batch_sizes=tuple(range(1, 65)))
+                       batch_sizes=tuple(range(1, 17)))
     it, want = O.Iterator(wl, ctx), O.Iterator(wl, ref)
     x = torch.zeros(64, device="cuda")
     want.build()
