@@ -1,14 +1,5 @@
-"""Chunked scoring: a (model, batch size) pair's prefix lengths split over
-several workgroups, each rebuilding the batch CDF of the prefixes before its
-chunk with warm-up steps.  Every chunk size must give the bits of the
-unsplit launch (the same fma sequence per bin), in both batch laws and both
-prefix modes; the automatic choice is checked against the oracle as well.
-Tabulated rows of more than two panels take every panel's E sums from the
-emax_kernel pre-pass when the launch is chunked (the chunks then repeat only
-the member panels): those cases must give the unsplit bits too."""
-import dataclasses
-import sys
-
+"""orloj_set_score_chunk: every setting is accepted and has no effect on the results, in
+launches that turned_kernel takes and in launches that score_kernel takes."""
 import numpy as np
 import pytest
 
@@ -20,24 +11,9 @@ from paper_2209_00159_amd import workloads as W
 pytestmark = pytest.mark.gpu
 
 
-def say(*a):
-    print(*a, flush=True)
-    sys.stdout.flush()
-
-
 @pytest.fixture(scope="module")
 def ctx():
-    c = O.Context()
-    yield c
-    c.set_score_chunk(-1)
-
-
-def run(wl, ctx, chunk, mode=0, trim=True):
-    ctx.set_score_chunk(chunk)
-    try:
-        return O.Scorer(wl, ctx, prefix_mode=mode, trim=trim).run(build=True)
-    finally:
-        ctx.set_score_chunk(-1)
+    return O.Context()
 
 
 def same_bits(a, b):
@@ -61,57 +37,60 @@ CASES = [
 
 @pytest.mark.parametrize("case", CASES, ids=lambda c: f"seed{c['seed']}")
 @pytest.mark.parametrize("law", ["tabulated", "affine"])
-def test_every_chunk_size_gives_the_same_bits(ctx, case, law):
-    say("chunks", law, case)
+def test_every_setting_on_both_kernels(ctx, case, law):
+    print("chunk settings", law, case, flush=True)
     wl = W.random_case(**case) if law == "tabulated" else W.random_affine(**case)
-    ref = run(wl, ctx, 0)
-    for ch in (1, 3, 8, 16, 32, -1):
-        same_bits(run(wl, ctx, ch), ref)
+    ora = (oracle.score_workload(wl) if law == "tabulated"
+           else oracle.score_workload_affine(wl, wl.c0_ms, wl.c1))
+    ref = O.Scorer(wl, ctx).run()
+    parity.compare(wl, ref, ora)
+    large = parity.on_score_kernel(wl, ctx, ora)
+    try:
+        ctx.set_score_chunk(8)
+        same_bits(O.Scorer(wl, ctx).run(), ref)
+        same_bits(parity.on_score_kernel(wl, ctx, ora), large)
+    finally:
+        ctx.set_score_chunk(-1)
 
 
 @pytest.mark.parametrize("seed", [20, 21])
-def test_rect_mode_chunks(ctx, seed):
+def test_rect_mode_on_both_kernels(ctx, seed):
     wl = W.random_case(seed, n_models=2, queue_lens=[90, 33], batch_sizes=(1, 8, 40),
                        n_bins=1500, tau_range=(-10.0, 1800.0))
-    ref = run(wl, ctx, 0, mode=1)
-    for ch in (7, 16, 64):
-        same_bits(run(wl, ctx, ch, mode=1), ref)
+    ora = oracle.score_workload(wl, prefix_mode=1)
+    parity.compare(wl, O.Scorer(wl, ctx, prefix_mode=1).run(), ora, mode=1)
+    parity.on_score_kernel(wl, ctx, ora, mode=1)
 
 
-def test_trimming_off_chunks(ctx):
+def test_trimming_off(ctx):
     wl = W.random_case(30, n_models=2, queue_lens=[64, 50], batch_sizes=(2, 32, 64),
                        n_bins=3000, tau_range=(-10.0, 4000.0))
-    ref = run(wl, ctx, 0, trim=False)
-    same_bits(run(wl, ctx, 8, trim=False), ref)
-    same_bits(run(wl, ctx, 8, trim=True), ref)
+    ora = oracle.score_workload(wl)
+    got = O.Scorer(wl, ctx).run()
+    parity.compare(wl, got, ora)
+    same_bits(O.Scorer(wl, ctx, trim=False).run(), got)
+    parity.on_score_kernel(wl, ctx, ora)
 
 
-def test_chunked_against_the_oracle(ctx):
+def test_config2(ctx):
     wl = W.make(2, slo_scale=3.0)
-    got = run(wl, ctx, 8)
-    err = parity.compare(wl, got, oracle.score_workload(wl))
-    say("  cfg2 x3, chunks of 8: max errors", err)
+    err = parity.compare(wl, O.Scorer(wl, ctx).run(), oracle.score_workload(wl))
+    print("  cfg2 x3: max errors", err)
 
 
-def test_config5_models_chunked(ctx):
+def test_config5_models(ctx):
     # eight models of the saturated state (four 1024-bin panels, 64 batch sizes)
     wl = W.make(5, models=[0, 17, 33, 50, 71, 90, 111, 127], workers=8)
-    ref = run(wl, ctx, 0)
-    for ch in (8, 16, 32, -1):
-        same_bits(run(wl, ctx, ch), ref)
+    parity.compare(wl, O.Scorer(wl, ctx).run(), oracle.score_workload(wl))
     aw = W.affine(wl)
-    ref = run(aw, ctx, 0)
-    same_bits(run(aw, ctx, 16), ref)
+    parity.compare(aw, O.Scorer(aw, ctx).run(), oracle.score_workload_affine(aw, aw.c0_ms, aw.c1))
 
 
 def test_small_config5_launch_against_the_oracle(ctx):
-    # the scheduling loop's shape: a few idle models, every batch size; the
-    # automatic choice chunks it and takes the E sums from the pre-pass
+    # the scheduling loop's shape: a few idle models, every batch size
     wl = W.make(5, models=[5, 64], workers=8, slo_scale=2.0)
-    got = run(wl, ctx, -1)
-    err = parity.compare(wl, got, oracle.score_workload(wl))
-    say("  cfg5, 2 models, automatic chunks: max errors", err)
-    same_bits(got, run(wl, ctx, 0))
+    err = parity.compare(wl, O.Scorer(wl, ctx).run(), oracle.score_workload(wl))
+    print("  cfg5, 2 models: max errors", err)
 
 
 def test_bad_chunk_is_rejected(ctx):

@@ -7,7 +7,8 @@ against the oracle.
   1024 apart in the tabulated mode, 256 apart in the affine mode's score
   waves), the grid's end K w (beyond the grid), and one ulp below each of
   them; runs of equal deadlines.  Tabulated and affine batch laws, both
-  prefix modes, every step-chunk setting giving the unsplit bits.
+  prefix modes; alone (turned_kernel) and over and over in one launch
+  (score_kernel).
 - The selection's tie rules (§3.2 Algorithm 1 pops one batch; equal scores
   go to the larger prefix, then to the smaller batch size): exact ties are
   built on purpose and the GPU's pick is asserted, not merely checked to
@@ -256,14 +257,10 @@ def ctx():
     return O.Context()
 
 
-def run_gpu(wl, ctx, mode=0, trim=True, chunk=-1):
+def run_gpu(wl, ctx, mode=0, trim=True):
     from paper_2209_00159_amd import orloj as O
-    ctx.set_score_chunk(chunk)
-    try:
-        sc = O.Scorer(wl, ctx, prefix_mode=mode, trim=trim)
-        return sc, sc.run(build=True)
-    finally:
-        ctx.set_score_chunk(-1)
+    sc = O.Scorer(wl, ctx, prefix_mode=mode, trim=trim)
+    return sc, sc.run(build=True)
 
 
 def same_bits(a, b):
@@ -278,13 +275,12 @@ def test_tabulated_milestones(ctx, i, mode):
     wl = tab_case(i, mode=mode)
     say(f"milestones K={wl.n_bins} mode={mode} members={wl.cls.size} bs={wl.batch_sizes.tolist()}")
     _, got = run_gpu(wl, ctx, mode=mode)
-    err = parity.compare(wl, got, oracle.score_workload(wl, prefix_mode=mode), mode=mode)
+    ora = oracle.score_workload(wl, prefix_mode=mode)
+    err = parity.compare(wl, got, ora, mode=mode)
     say("  max errors", err)
-    for ch in (0, 3, 8):
-        _, g2 = run_gpu(wl, ctx, mode=mode, chunk=ch)
-        same_bits(got, g2)
     _, g3 = run_gpu(wl, ctx, mode=mode, trim=False)
     same_bits(got, g3)
+    parity.on_score_kernel(wl, ctx, ora, mode)
 
 
 @gpu
@@ -297,9 +293,7 @@ def test_affine_milestones(ctx, below, mode):
     ora = oracle.score_workload_affine(aw, aw.c0_ms, aw.c1, prefix_mode=mode)
     err = parity.compare(aw, got, ora, mode=mode)
     say("  max errors", err)
-    for ch in (0, 8):
-        _, g2 = run_gpu(aw, ctx, mode=mode, chunk=ch)
-        same_bits(got, g2)
+    parity.on_score_kernel(aw, ctx, ora, mode)
 
 
 @gpu
@@ -350,8 +344,8 @@ def test_coherent_expected_finish(ctx, n, theta, bs):
 # mass sits in a window (so whole panels lie before a row's first bin with
 # mass, where G becomes 0, or after its last, where the row is 0): a cached
 # class's first member then falls on skipped steps, and its later members
-# must still see this pass's slice.  Ragged and exact grids, chunked launches
-# whose warm-up steps take the cached path too.
+# must still see this pass's slice.  Ragged and exact grids.  The models alone
+# go to turned_kernel; the copies are score_kernel's, over and over in one launch.
 # ---------------------------------------------------------------------------
 def window_counts(rng, B, C, K, total=TOTAL):
     """[B, C, K] counts: each row's mass spread over a window of random start
@@ -416,9 +410,7 @@ def test_mixed_member_panels_cached_slices(ctx, seed, K):
     say(f"  max errors {err}")
     _, untrimmed = run_gpu(wl, ctx, trim=False)
     same_bits(got, untrimmed)
-    for chunk in (0, 8):
-        _, split = run_gpu(wl, ctx, chunk=chunk)
-        same_bits(got, split)
+    parity.on_score_kernel(wl, ctx, ora)
 
 
 @gpu
@@ -433,6 +425,4 @@ def test_repeated_classes_cached_slices(ctx, seed, K):
     say(f"  max errors {err}")
     _, untrimmed = run_gpu(wl, ctx, trim=False)
     same_bits(got, untrimmed)
-    for chunk in (0, 8):
-        _, split = run_gpu(wl, ctx, chunk=chunk)
-        same_bits(got, split)
+    parity.on_score_kernel(wl, ctx, ora)

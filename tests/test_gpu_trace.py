@@ -107,10 +107,10 @@ def test_native_runtime_rounds():
 
 
 def test_native_round_selections_equal_the_public_calls():
-    """The runtime scores a round through its own launch (the E pre-pass and
-    the score waves together, E[L_B] and the scores finished by the
-    selection); its selections must be those of orloj_score_candidates +
-    orloj_select_batch on the same queue, exactly (the same bits decide)."""
+    """The runtime scores and selects every idle model in one round; its
+    selections must be those of orloj_score_candidates + orloj_select_batch on
+    the model's queue alone.  (The launches may differ in size and with it in
+    the scores' last bits: a pick would differ only between scores that close.)"""
     ctx = O.Context()
     models = list(range(8))
     say("config 5 native loop: 8 models, 2000 arrivals, every decision recorded")

@@ -80,22 +80,9 @@ def test_both_kernels_against_the_oracle(ctx, case, law):
     parity.compare(one, small, ora, mode=mode)
     # the same models over and over: in one launch of more workgroups than compute units
     # (four waves each), and in one of more than turned_kernel takes
-    M = one.n_models
-    caps = [[one.queue_len(q) if mode else min(one.queue_len(q), int(s)) for s in one.batch_sizes]
-            for q in range(M)]
-    groups, longest = sum((c + 63) // 64 for cs in caps for c in cs), max(max(cs) for cs in caps)
-    for most in (N_CU, past_turned(law, one.n_bins, longest)):
+    groups, longest = parity.turned_groups(one, mode)
+    for most in (parity.N_CU, parity.past_turned(law == "affine", one.n_bins, longest)):
         check_large(ctx, one, mode, most // groups + 1, small, ora)
-
-
-N_CU = 256
-
-
-def past_turned(law, n_bins, longest):
-    """Workgroups that turned_kernel does not take more of, whatever else holds."""
-    if law == "affine":
-        return 2 * N_CU + 24 * longest
-    return max(2 * N_CU, (20 + 11 * -(-n_bins // 1024)) * longest)
 
 
 def check_large(ctx, one, mode, reps, small, ora):
