@@ -194,6 +194,12 @@ int orloj_output_sizes(const orloj_grid *grid, const orloj_queues *queues,
  * buffers hold at least n_cands / n_probs elements.  b_expo_per_ms must be
  * finite and > 0 (the paper uses 1e-4 per ms, §4.4).
  * ORLOJ_E_UNSUPPORTED when a prefix would exceed ORLOJ_MAX_PREFIX.
+ * A call's results are the same bits every time, eager or captured, with
+ * d_support or without.  Calls of different sizes take different kernels: the
+ * number of queues filled, the longest prefix and the grid decide, so a model's
+ * results may differ in their last bits between a call for it alone and one for
+ * many models: P by up to 2^-24, the expected finish count by 1e-12, E[L_B] by
+ * 2^-21 and the score by as much as E[L_B], relative.  The affine calls likewise.
  */
 int orloj_score_candidates(orloj_ctx *ctx, const orloj_grid *grid, const float *d_ccdf,
                            const int32_t *d_support, const orloj_queues *queues, double b_expo_per_ms,
