@@ -100,3 +100,18 @@ def check_large(ctx, one, mode, reps, small, ora):
         # E[L_B]: score_kernel adds fp32 sums, each rounded once per panel
         # (2^-25 of it) after a six-level fp32 tree (6 x 2^-24)
         assert np.allclose(part["expected_latency_ms"], small["expected_latency_ms"], rtol=8 * 2.0**-24, atol=0)
+
+
+@pytest.mark.parametrize("law", ["tabulated", "affine"])
+@pytest.mark.parametrize("every", [4, 10])
+def test_mostly_empty_launches(ctx, law, every):
+    """300 models with a queue, too many to list, among 1200 (turned_kernel, with workgroups
+    that find nothing to do) and among 3000 (score_kernel: most would)."""
+    print("mostly empty", law, every, flush=True)
+    n = 300 * every
+    case = dict(seed=130 + every, n_models=n, n_classes=2, n_bins=40, batch_sizes=(14,),
+                queue_lens=[14 if q % every == every - 1 else 0 for q in range(n)])
+    wl = W.random_affine(**case) if law == "affine" else W.random_case(**case)
+    ora = (oracle.score_workload_affine(wl, wl.c0_ms, wl.c1) if law == "affine"
+           else oracle.score_workload(wl))
+    parity.compare(wl, run(wl, ctx, 0, True), ora)
